@@ -7,7 +7,7 @@
 // (re, im) int samples, and the weight matrix has blocks
 // [[w_re, w_im], [-w_im, w_re]].  LP_FP16_MFMA converts the ints to FP16
 // (exact for int8) and accumulates in FP32 with v_mfma_f32_16x16x16f16;
-// LP_FP32 does the same sums on the vector ALUs.
+// LP_FP32 does the same sums in FP32 with v_mfma_f32_16x16x4_f32.
 #include <cmath>
 #include <cstring>
 #include <type_traits>
@@ -314,77 +314,170 @@ __global__ __launch_bounds__(kBfThreads) void bf_mfma_kernel(
 
 // --------------------------------------------------------- FP32 kernel
 
-constexpr int kBf32Group = 8;  // beams accumulated per pass over a row
+// Four consecutive samples (one k-group of a lane) as FP32, exact.
+template <typename IT>
+__device__ __forceinline__ void group_to_f32(const unsigned *w, float *f) {
+  if constexpr (sizeof(IT) == 1) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) f[i] = (float)(signed char)(w[0] >> (8 * i));
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      f[i] = (float)(short)(w[i >> 1] >> (16 * (i & 1)));
+  }
+}
 
-// Grid: x = tiles of T = 256 / G time rows, y = subband.  The tile's raw
-// integer samples are staged in LDS with a row stride that is an odd
-// number of 32-bit words (conflict-free row-per-lane reads); the weights
-// [K][B] follow.  Thread (t, g) forms beams 8g .. 8g + 7, 8(g + G) .. for
-// time row t, eight beams per pass over the row.
-template <typename IT, int VB>
-__global__ __launch_bounds__(kBfThreads) void bf_fp32_kernel(
+// NW words of a raw buffer at byte offset off, in loads of W words.
+template <int NW, int W>
+__device__ __forceinline__ void buffer_words(__amdgpu_buffer_rsrc_t rs,
+                                             unsigned off, unsigned *w) {
+  typedef unsigned u4 __attribute__((ext_vector_type(4)));
+  typedef unsigned u2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+  for (int i = 0; i < NW; i += W) {
+    if constexpr (W == 4) {
+      const u4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 4 * i, 0);
+      w[i] = v.x; w[i + 1] = v.y; w[i + 2] = v.z; w[i + 3] = v.w;
+    } else if constexpr (W == 2) {
+      const u2 v = __builtin_amdgcn_raw_buffer_load_b64(rs, off, 4 * i, 0);
+      w[i] = v.x; w[i + 1] = v.y;
+    } else {
+      w[i] = __builtin_amdgcn_raw_buffer_load_b32(rs, off, 4 * i, 0);
+    }
+  }
+}
+
+// LP_FP32: the same real GEMM on the FP32 matrix instructions (FP32 inputs,
+// weights and accumulation).  What bounds it is the FP32 multiply rate, 32
+// FMA per cycle and SIMD; the vector-ALU kernel it replaces read its weights
+// from LDS once per beam and input and reached 1/15 of that (96 int16 inputs,
+// 37 beams, 122 x 8192 samples: 2716 -> 267 us, 106 TFLOP/s; one beam of 48
+// int8 inputs, 122 x 16384: 77 -> 71 us, bound by memory).
+//
+// A wave owns pieces of 16 MT rows of one subband and walks the 16-column
+// n-tiles; the subband's weights sit in LDS as B fragments.  A workgroup
+// takes a contiguous range of the subband-major list of pieces (about one
+// workgroup per slot of the chip, so there is no last round) and fills the
+// weights anew where its range enters a subband.  The order of the k index
+// is free, so lane (row, q) of an A fragment takes samples q 4 GM .. q 4 GM +
+// 4 GM - 1 of its row, one contiguous piece that it loads itself (no LDS, no
+// barrier between subbands) one step ahead and converts once for all n-tiles.
+// Samples past the row's 2 K meet zero weights; the raw buffer view ends with
+// the piece, where reads return zero.  Loads are as wide as divides both a
+// lane's part and the row, so that none lies across that end; rows of other
+// lengths are read word by word.
+template <typename IT, int GM, int MT>
+__global__ __launch_bounds__(512) void bf_fp32_kernel(
     const IT *__restrict__ x, const float2 *__restrict__ w,
     float2 *__restrict__ y, int n_sb, long n_t, long x_nt, int n_in,
-    int n_beams, int row_words, int G) {
-  extern __shared__ int smi[];
-  const int T = kBfThreads / G;
-  const int RK = 2 * n_in;
-  const int row_bytes = RK * (int)sizeof(IT);
-  int *xs = smi;                                        // [T][row_words]
-  float2 *ws = reinterpret_cast<float2 *>(smi + T * row_words);
-  const int s = blockIdx.y;
-  const long t0 = (long)blockIdx.x * T;
-  const int rows = (int)min((long)T, n_t - t0);
-  const char *base =
-      reinterpret_cast<const char *>(x + ((long)s * x_nt + t0) * RK);
-  const int vec_per_row = row_bytes / VB;
-  const int nvec = rows * vec_per_row;
-  for (int v = threadIdx.x; v < nvec; v += kBfThreads) {
-    int row = v / vec_per_row, c = v - row * vec_per_row;
-    int q[VB / 4];
-    __builtin_memcpy(q, base + (size_t)v * VB, VB);
+    int n_beams, int NT, long per_wg) {
+  extern __shared__ __attribute__((aligned(16))) float wl[];
+  constexpr int NW = 4 * GM * (int)sizeof(IT) / 4;  // words per lane and row
+  constexpr int W = NW % 4 == 0 ? 4 : NW % 2 == 0 ? 2 : 1;
+  const int tid = threadIdx.x, nthr = blockDim.x;
+  const int wave = tid >> 6, lane = tid & 63;
+  const int col16 = lane & 15, q = lane >> 4;
+  const unsigned row_bytes = 2u * n_in * sizeof(IT);
+  const bool wide = row_bytes % (4 * W) == 0;
+  const int per_sb = (int)(n_t / (16 * MT));  // pieces of a subband
+  const long total = (long)per_sb * n_sb;
+  long g = (long)blockIdx.x * per_wg;
+  const long g_end = min(g + per_wg, total);
+
+  while (g < g_end) {
+    const int s = (int)(g / per_sb);
+    const int p0 = (int)(g - (long)s * per_sb);
+    const int p1 = (int)min((long)per_sb, p0 + (g_end - g));
+    g += p1 - p0;
+
+    unsigned raw[MT][NW];
+    auto fetch = [&](int p) {
+      const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+          const_cast<IT *>(x) + ((long)s * x_nt + (long)p * 16 * MT) * 2 * n_in,
+          0, (int)(16 * MT * row_bytes), kRawBufferWord3);
 #pragma unroll
-    for (int i = 0; i < VB / 4; ++i) xs[row * row_words + c * (VB / 4) + i] = q[i];
-  }
-  const float2 *wsrc = w + (long)s * n_in * n_beams;
-  for (int i = threadIdx.x; i < n_in * n_beams; i += kBfThreads) ws[i] = wsrc[i];
-  __syncthreads();
-  const int t = threadIdx.x % T, g = threadIdx.x / T;
-  if (t >= rows) return;
-  const int *xr = xs + t * row_words;
-  for (int b0 = kBf32Group * g; b0 < n_beams; b0 += kBf32Group * G) {
-    float ar[kBf32Group], ai[kBf32Group];
-#pragma unroll
-    for (int k = 0; k < kBf32Group; ++k) ar[k] = ai[k] = 0.f;
-    for (int i = 0; i < n_in; ++i) {
-      float re, im;
-      if constexpr (sizeof(IT) == 1) {
-        int word = xr[i >> 1];
-        int sh = (i & 1) * 16;
-        re = (float)(signed char)(word >> sh);
-        im = (float)(signed char)(word >> (sh + 8));
-      } else {
-        int word = xr[i];
-        re = (float)(short)(word & 0xffff);
-        im = (float)(short)(word >> 16);
+      for (int m = 0; m < MT; ++m) {
+        const unsigned off = (16 * m + col16) * row_bytes + q * (4 * NW);
+        if (wide)
+          buffer_words<NW, W>(rs, off, raw[m]);
+        else
+          buffer_words<NW, 1>(rs, off, raw[m]);
       }
-      const float2 *wi = ws + i * n_beams + b0;
+    };
+    int piece = p0 + wave;
+    if (piece < p1) fetch(piece);
+
+    // Weight k = q 4 GM + 4 g + i of column 16 nt + c is element
+    // ((nt GM + g) 64 + 16 q + c) 4 + i; zero outside the inputs and beams.
+    __syncthreads();  // the previous subband's weights are done with
+    for (int i = tid; i < NT * GM * 64; i += nthr)
+      reinterpret_cast<floatx4 *>(wl)[i] = floatx4{0, 0, 0, 0};
+    __syncthreads();
+    const float2 *ws = w + (long)s * n_in * n_beams;
+    for (int i = tid; i < n_in * n_beams; i += nthr) {
+      const int inp = i / n_beams, b = i - inp * n_beams;
+      const float2 v = ws[i];
+      const int k = 2 * inp, qk = k / (4 * GM), r = k - qk * 4 * GM;
+      float *e = wl + (((b >> 3) * GM + (r >> 2)) * 64 + 16 * qk +
+                       ((2 * b) & 15)) * 4 + (r & 3);
+      e[0] = v.x;   // re of the sample, real column
+      e[1] = -v.y;  // im of the sample, real column
+      e[4] = v.y;   // re, imaginary column
+      e[5] = v.x;   // im, imaginary column
+    }
+    __syncthreads();
+
+    for (; piece < p1; piece += nthr / 64) {
+      float a[MT][4 * GM];
 #pragma unroll
-      for (int k = 0; k < kBf32Group; ++k) {
-        if (b0 + k < n_beams) {
-          float2 wv = wi[k];
-          ar[k] = fmaf(re, wv.x, ar[k]);
-          ar[k] = fmaf(-im, wv.y, ar[k]);
-          ai[k] = fmaf(re, wv.y, ai[k]);
-          ai[k] = fmaf(im, wv.x, ai[k]);
+      for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int gi = 0; gi < GM; ++gi)
+          group_to_f32<IT>(raw[m] + gi * (int)sizeof(IT), a[m] + 4 * gi);
+      if (piece + nthr / 64 < p1) fetch(piece + nthr / 64);
+      // Lane holds D[4 q + r][col16] as in the FP16 kernel: pairs of lanes
+      // store two complex samples each of their beam (8 beams per n-tile).
+      const bool odd = col16 & 1;
+      float2 *yp = y + ((long)(col16 >> 1) * n_sb + s) * n_t +
+                   (long)piece * 16 * MT + 4 * q + (odd ? 2 : 0);
+      const floatx4 *wf = reinterpret_cast<const floatx4 *>(wl) + lane;
+      floatx4 bw = wf[0];
+      for (int nt = 0; nt < NT; ++nt, yp += 8L * n_sb * n_t) {
+        floatx4 acc[MT];
+#pragma unroll
+        for (int m = 0; m < MT; ++m) acc[m] = floatx4{0, 0, 0, 0};
+#pragma unroll
+        for (int gi = 0; gi < GM; ++gi) {
+          // The next group's weights (at the end the next n-tile's; the last
+          // tile reads its own again) are in flight behind this group's
+          // products: read in place, every group waited for the LDS (277 us
+          // against 268 at 96 int16 inputs, 37 beams, 122 x 8192 samples).
+          if (gi + 1 < GM || nt + 1 < NT) wf += 64;
+          const floatx4 nx = *wf;
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int m = 0; m < MT; ++m)
+              acc[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                  a[m][4 * gi + i], bw[i], acc[m], 0, 0, 0);
+          bw = nx;
+        }
+#pragma unroll
+        for (int m = 0; m < MT; ++m) {
+          const float a0 = acc[m][0], a1 = acc[m][1], a2 = acc[m][2],
+                      a3 = acc[m][3];
+          const float n0 = lane_swap1(a0), n1 = lane_swap1(a1),
+                      n2 = lane_swap1(a2), n3 = lane_swap1(a3);
+          if (nt * 8 + (col16 >> 1) < n_beams) {
+            const floatx4 o = {odd ? n2 : a0, odd ? a2 : n0, odd ? n3 : a1,
+                               odd ? a3 : n1};
+            __builtin_nontemporal_store(
+                o, reinterpret_cast<floatx4 *>(yp + 16 * m));
+          }
         }
       }
     }
-#pragma unroll
-    for (int k = 0; k < kBf32Group; ++k)
-      if (b0 + k < n_beams)
-        y[((long)(b0 + k) * n_sb + s) * n_t + t0 + t] =
-            make_float2(ar[k], ai[k]);
   }
 }
 
@@ -470,6 +563,7 @@ lp_status get_bf_plan(lp_ctx *ctx, const lp_array *a, const lp_band *band,
   p->KS = (2 * n_in + 15) / 16;
   p->NT = (2 * n_beams + 15) / 16;
   p->scaled = scaled;
+  p->n_cu = ctx->n_cu;
 
   // Descriptor copies for the weight kernel, one upload: enu, az/el,
   // weight scale (f64), then subband ids, gains, groups (32-bit).
@@ -605,35 +699,49 @@ static lp_status launch_bf(const BfPlan *p, const void *x, long x_nt,
     }
     if (rc) return rc;
   } else {
-    int row_words = row_bytes / 4;
-    if (row_words % 2 == 0) row_words += 1;  // odd stride: no bank conflicts
-    // Rows per tile: 256, halved (with G = 256 / T threads sharing a row's
-    // beam groups) until the tile and the weights fit in LDS.
-    int T = kBfThreads, G = 1;
-    auto lds = [&](int T_) {
-      return (size_t)T_ * row_words * 4 + (size_t)n_in * p->n_beams * 8;
-    };
-    while (lds(T) > kLdsMax && T > 32) {
-      T /= 2;
-      G *= 2;
-    }
-    size_t shm = lds(T);
-    if (shm > kLdsMax)
-      return set_error(LP_EINVAL, "FP32 beamformer tile too large for LDS");
-    dim3 grid((unsigned)((n_t + T - 1) / T), n_sb);
-    auto args = [&](auto kern) {
+    // k-groups of four samples per lane quarter (the kernel instance's; more
+    // inputs than 16 GM / 2 need the next one up).
+    const int g_need = (RK + 15) / 16;
+    const int NT = p->NT;
+    auto args = [&](auto kern, int gm, int mt) {
+      // Workgroups per CU by the weights' LDS and the registers (two waves
+      // per SIMD from GM = 9 on, more below); where the weights take more
+      // than half of the LDS, one workgroup of 8 waves.
+      const size_t shm = (size_t)NT * gm * 1024;
+      const int threads = shm > kLdsMax / 2 ? 512 : 256, waves = threads / 64;
+      const int by_regs = gm <= 2 ? 8 : gm <= 4 ? 4 : gm <= 8 ? 3 : 2;
+      const long slots =
+          (long)p->n_cu * (threads == 512 ? 1 : std::min<long>(by_regs, kLdsMax / shm));
+      const long total = n_t / (16 * mt) * n_sb;
+      long per_wg = (total + slots - 1) / slots;
+      // Whole steps of the workgroup's waves, unless a subband is shorter
+      // than that (then a range of two subbands would only fill twice).
+      if (n_t / (16 * mt) >= waves) per_wg = (per_wg + waves - 1) / waves * waves;
+      const long n_wg = (total + per_wg - 1) / per_wg;
       LP_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                  hipFuncAttributeMaxDynamicSharedMemorySize,
                                  (int)shm));
-      hipLaunchKernelGGL(kern, grid, dim3(kBfThreads), shm, st,
+      hipLaunchKernelGGL(kern, dim3((unsigned)n_wg), dim3(threads), shm, st,
                          static_cast<const IT *>(x), p->w.as<const float2>(),
                          static_cast<float2 *>(y), n_sb, n_t, x_nt, n_in,
-                         p->n_beams, row_words, G);
+                         p->n_beams, NT, per_wg);
       return LP_OK;
     };
-    lp_status rc = (vb == 16)  ? args(bf_fp32_kernel<IT, 16>)
-                   : (vb == 8) ? args(bf_fp32_kernel<IT, 8>)
-                               : args(bf_fp32_kernel<IT, 4>);
+    // Rows per piece: 64 while the registers allow (short rows are bound by
+    // memory and want more loads in flight), else 32.
+    lp_status rc = g_need <= 1    ? args(bf_fp32_kernel<IT, 1, 4>, 1, 4)
+                   : g_need <= 2  ? args(bf_fp32_kernel<IT, 2, 4>, 2, 4)
+                   : g_need <= 3  ? args(bf_fp32_kernel<IT, 3, 4>, 3, 4)
+                   : g_need <= 4  ? args(bf_fp32_kernel<IT, 4, 4>, 4, 4)
+                   : g_need <= 5  ? args(bf_fp32_kernel<IT, 5, 2>, 5, 2)
+                   : g_need <= 6  ? args(bf_fp32_kernel<IT, 6, 2>, 6, 2)
+                   : g_need <= 7  ? args(bf_fp32_kernel<IT, 7, 2>, 7, 2)
+                   : g_need <= 8  ? args(bf_fp32_kernel<IT, 8, 2>, 8, 2)
+                   : g_need <= 9  ? args(bf_fp32_kernel<IT, 9, 2>, 9, 2)
+                   : g_need <= 10 ? args(bf_fp32_kernel<IT, 10, 2>, 10, 2)
+                   : g_need <= 12 ? args(bf_fp32_kernel<IT, 12, 2>, 12, 2)
+                   : g_need <= 14 ? args(bf_fp32_kernel<IT, 14, 2>, 14, 2)
+                                  : args(bf_fp32_kernel<IT, 16, 2>, 16, 2);
     if (rc) return rc;
   }
   LP_HIP(hipGetLastError());

@@ -130,6 +130,7 @@ struct BfPlan : PlanBase {
   int prec = 0;
   int n_in = 0, n_beams = 0, n_sb = 0;
   int KS = 0, NT = 0;        // MFMA: k-steps of 16 real rows, n-tiles of 16
+  int n_cu = 256;            // compute units of the context's device
   bool scaled = false;       // per-input power-of-two input scaling in use
   DevBuf params;             // descriptor copies the weight kernel reads
   DevBuf w;                  // FP16 MFMA fragments or FP32 [s][in][b]
