@@ -8,10 +8,10 @@
 //
 // One 256-thread workgroup per (beam, subband, hop).  Each thread owns 16
 // points; the 4096-point transform is three radix-16 Stockham passes with
-// two exchanges through a padded 34 KB LDS tile.  Each thread's base
-// twiddle of a pass comes from two small LDS tables and its powers from a
-// product tree (tables of all powers were measured slower: this kernel is
-// close to bound by LDS instructions as well as VALU).  The forward
+// two exchanges through a padded 34 KB LDS tile.  The butterflies take the
+// powers 1, 2, 4 and 8 of a pass's twiddle, each rounded from the exact value:
+// pass 1's from a small LDS table, pass 2's per thread (tables of all 15 powers were measured slower: this
+// kernel is close to bound by LDS instructions as well as VALU).  The forward
 // spectrum stays in registers across all trials.  A trial's chirp phase is
 // formed per bin from FP64-reduced constants and taken through the
 // hardware sine and cosine; on a uniform grid only the first trial's is,
@@ -29,78 +29,32 @@ namespace lp {
 constexpr int kDdThreads = 256;
 constexpr int kDdLds = 4096 + 128;  // slot of element 4095 is 4222
 
-// 16-point DFT returning only outputs 8..15 (in v[8..15]; v[0..7] are left
-// undefined): the second radix-4 stage forms just its outputs 2 and 3.
-template <bool INV>
-__device__ __forceinline__ void dft16_hi(float2 *v) {
-#pragma unroll
-  for (int n2 = 0; n2 < 4; ++n2) dft4<INV>(v[n2], v[4 + n2], v[8 + n2], v[12 + n2]);
-#pragma unroll
-  for (int n2 = 1; n2 < 4; ++n2) {
-#pragma unroll
-    for (int k1 = 1; k1 < 4; ++k1)
-      v[n2 + 4 * k1] = tw16<INV>(v[n2 + 4 * k1], n2 * k1);
-  }
-  float2 o[8];
-#pragma unroll
-  for (int k1 = 0; k1 < 4; ++k1) {
-    const float2 a = v[4 * k1], b = v[4 * k1 + 1], c = v[4 * k1 + 2],
-                 d = v[4 * k1 + 3];
-    const float2 t0 = cadd(a, c), t1 = csub(a, c), t2 = cadd(b, d),
-                 t3 = csub(b, d);
-    o[k1] = csub(t0, t2);  // output k1 + 8
-    // output k1 + 12: t1 + i t3 (forward) or t1 - i t3 (inverse)
-    o[4 + k1] = INV ? make_float2(t1.x + t3.y, t1.y - t3.x)
-                    : make_float2(t1.x - t3.y, t1.y + t3.x);
-  }
-#pragma unroll
-  for (int i = 0; i < 8; ++i) v[8 + i] = o[i];
-}
-
-// v[r] *= w^r (r = 1..15), the powers formed by a product tree of depth 4
-// and each used as soon as it exists (few live registers, short chains).
-__device__ __forceinline__ void pow16_twiddle(float2 *v, const float2 w1) {
-  const float2 w2 = cmul(w1, w1), w4 = cmul(w2, w2), w8 = cmul(w4, w4);
-  const float2 w3 = cmul(w2, w1);
-  v[1] = cmul(v[1], w1);
-  v[2] = cmul(v[2], w2);
-  v[3] = cmul(v[3], w3);
-  v[4] = cmul(v[4], w4);
-  v[5] = cmul(v[5], cmul(w4, w1));
-  v[6] = cmul(v[6], cmul(w4, w2));
-  const float2 w7 = cmul(w4, w3);
-  v[7] = cmul(v[7], w7);
-  v[8] = cmul(v[8], w8);
-  v[9] = cmul(v[9], cmul(w8, w1));
-  v[10] = cmul(v[10], cmul(w8, w2));
-  v[11] = cmul(v[11], cmul(w8, w3));
-  v[12] = cmul(v[12], cmul(w8, w4));
-  v[13] = cmul(v[13], cmul(w8, cmul(w4, w1)));
-  v[14] = cmul(v[14], cmul(w8, cmul(w4, w2)));
-  v[15] = cmul(v[15], cmul(w8, w7));
-}
-
-// LDS twiddle tables of one workgroup (w = exp(-2 pi i / 4096)):
-//   coarse[c] = w^(16 c) (c < 256), fine[f] = w^f (f < 16).
+// Pass-1 twiddles of one workgroup (w = exp(-2 pi i / 4096)): w^(16 a) and
+// its powers 2, 4, 8 for a < 16.
 struct DdTw {
-  float2 coarse[256];
-  float2 fine[16];
+  Tw16 p1[16];
 };
 
 // 4096-point transform of v[r] = in[j + 256 r] (j = thread); on return
 // v[r] = out[j + 256 r] (HI: only r >= 8).  Unnormalised; INV selects
 // exp(+2 pi i ...).
-template <bool INV, bool HI>
+// pass2_twiddle(j) gives w^j and its powers.  START: pass 0's first stage (the pairs v[n], v[n + 8]) is done.
+template <bool INV, bool HI, bool START, typename Pass2>
 __device__ __forceinline__ void fft4096(float2 *v, float2 *lds,
-                                        const DdTw &tw, int j) {
+                                        const DdTw &tw, Pass2 pass2_twiddle,
+                                        int j) {
   // Element e sits at slot e + e / 32 (one pad slot per 32: every access
   // pattern below puts the 64 lanes' 8-byte words evenly on the banks, for
   // 32 or 64 banks).  In closed form (j < 256, r < 16):
   //   16 j + r -> 16 j + j / 2 + r,  j + 256 r -> j + j / 32 + 264 r,
   //   (j / 16) 256 + j mod 16 + 16 r -> (j / 16) 264 + j mod 16 + 16 r + r / 2.
   const int sj = j + (j >> 5);
-  // Pass 0 (Ns = 1): no twiddle; write to (16 j + r).
-  dft16<INV>(v);
+  // Pass 0 (Ns = 1): no twiddle; write to (16 j + r) once every thread has
+  // read the previous transform's last exchange.
+  if (START)
+    dft16_tail<INV, 16>(v);
+  else
+    dft16_fma<INV>(v);
   __syncthreads();
   {
     const int b0 = 16 * j + (j >> 1);
@@ -111,11 +65,8 @@ __device__ __forceinline__ void fft4096(float2 *v, float2 *lds,
   // Pass 1 (Ns = 16): twiddle w^(16 (j mod 16) r).
 #pragma unroll
   for (int r = 0; r < 16; ++r) v[r] = lds[sj + 264 * r];
-  {
-    const float2 w = tw.coarse[j & 15];
-    pow16_twiddle(v, INV ? make_float2(w.x, -w.y) : w);
-  }
-  dft16<INV>(v);
+  dft16_twiddled<INV>(v, tw.p1[j & 15].conj_if<INV>());
+  const Tw16 w2p = pass2_twiddle(j);
   __syncthreads();
   {
     const int b2 = (j >> 4) * 264 + (j & 15);
@@ -127,14 +78,7 @@ __device__ __forceinline__ void fft4096(float2 *v, float2 *lds,
   // registers.
 #pragma unroll
   for (int r = 0; r < 16; ++r) v[r] = lds[sj + 264 * r];
-  {
-    const float2 w = cmul(tw.coarse[j >> 4], tw.fine[j & 15]);
-    pow16_twiddle(v, INV ? make_float2(w.x, -w.y) : w);
-  }
-  if (HI)
-    dft16_hi<INV>(v);
-  else
-    dft16<INV>(v);
+  dft16_twiddled<INV, HI>(v, w2p.conj_if<INV>());
 }
 
 // Chirp factor exp(-2 pi i c) for a phase c in cycles, |c| <= 1/2 after the
@@ -142,6 +86,13 @@ __device__ __forceinline__ void fft4096(float2 *v, float2 *lds,
 __device__ __forceinline__ float2 chirp(float c) {
   c -= rintf(c);
   return make_float2(__builtin_amdgcn_cosf(c), -__builtin_amdgcn_sinf(c));
+}
+
+// base + e folded into [-1/2, 1/2] with one rounding: e (a multiple of 1/4)
+// less a whole number is exact.  Near zero a phase keeps more bits (the
+// outputs' error against 64 bits is set by this rounding).
+__device__ __forceinline__ float fold_phase(float base, float e) {
+  return base + (e - rintf(base + e));
 }
 
 // REC: the trials are uniformly spaced, so the first trial's chirp comes
@@ -157,11 +108,26 @@ __attribute__((amdgpu_waves_per_eu(4, 8))) void dd_kernel(
     int n_tec, long n_t, int n_hop, long n_blocks) {
   __shared__ float2 lds[kDdLds];
   __shared__ DdTw tws;
-  {
-    const int i = threadIdx.x;  // tw[n] = w^n, n < 4096
-    tws.coarse[i] = tw[16 * i];
-    if (i < 16) tws.fine[i] = tw[i];
+  if (threadIdx.x < 16) {  // tw[n] = w^n, n < 4096
+    const int i = 16 * threadIdx.x;
+    tws.p1[threadIdx.x] = {tw[i], tw[2 * i], tw[4 * i], tw[8 * i]};
   }
+  // The pass-2 twiddle w^j: kept in registers, except beside the trial
+  // steps' 32 (REC), where each pass reads it again (8 KB, from the caches)
+  // ahead of the exchange.
+  const Tw16 w2p = {tw[threadIdx.x], tw[2 * threadIdx.x], tw[4 * threadIdx.x],
+                    tw[8 * threadIdx.x]};
+  const __amdgpu_buffer_rsrc_t twrs = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<float2 *>(tw), 0, kNfft * 8, kRawBufferWord3);
+  auto pass2_twiddle = [&](int jo) {
+    if constexpr (!REC) return w2p;
+    auto at = [&](int n) {
+      typedef unsigned u2 __attribute__((ext_vector_type(2)));
+      const u2 b = __builtin_amdgcn_raw_buffer_load_b64(twrs, 8 * n, 0, 0);
+      return make_float2(__uint_as_float(b.x), __uint_as_float(b.y));
+    };
+    return Tw16{at(jo), at(2 * jo), at(4 * jo), at(8 * jo)};
+  };
   // (the barrier inside the first transform orders these before use)
   const long bid = xcd_remap(blockIdx.x, n_blocks);
   const int h = (int)(bid % n_hop);
@@ -180,7 +146,7 @@ __attribute__((amdgpu_waves_per_eu(4, 8))) void dd_kernel(
 #pragma unroll
   for (int r = 8; r < 16; ++r) v[r] = ys[hs + j + 256 * (r - 8)];
 
-  fft4096<false, false>(v, lds, tws, j);
+  fft4096<false, false, false>(v, lds, tws, pass2_twiddle, j);
 
   // Hop 0 read the old tail above (and every thread has passed the
   // barriers inside the transform), so it can now store the new one.
@@ -208,7 +174,7 @@ __attribute__((amdgpu_waves_per_eu(4, 8))) void dd_kernel(
   const long trial_stride = (long)n_sb * n_t;
   if (REC) {
     // U becomes the first trial's chirped spectrum; R the per-trial factor.
-    const float bse = base[s] + e, A = afac[s];
+    const float bse = fold_phase(base[s], e), A = afac[s];
     const float2 *rs = rstep + s * kNfft + j;
     float2 R[16];
 #pragma unroll
@@ -225,8 +191,7 @@ __attribute__((amdgpu_waves_per_eu(4, 8))) void dd_kernel(
         v[r] = U[r];
         U[r] = cmul(U[r], R[r]);
       }
-      __syncthreads();  // previous trial's last LDS reads are done
-      fft4096<true, true>(v, lds, tws, jo);
+      fft4096<true, true, false>(v, lds, tws, pass2_twiddle, jo);
       float2 *out = outb + jt * trial_stride;
 #pragma unroll
       for (int r = 8; r < 16; ++r) out[256 * (r - 8)] = v[r];
@@ -234,20 +199,110 @@ __attribute__((amdgpu_waves_per_eu(4, 8))) void dd_kernel(
   } else {
     for (int jt = 0; jt < n_tec; ++jt) {
       const int jo = opaque(j);
-      const float bse = base[jt * n_sb + s] + e, A = afac[jt * n_sb + s];
+      const float bse = fold_phase(base[jt * n_sb + s], e),
+                  A = afac[jt * n_sb + s];
       const int goff = 4 * (s * kNfft + jo);
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
+      // The chirped spectrum and the inverse's first stage together: the
+      // chirp factor of bin n + 8 is the twiddle of that butterfly.
+      auto factor = [&](int r) {
         const float g = __uint_as_float(
             __builtin_amdgcn_raw_buffer_load_b32(grs, goff, 1024 * r, 0));
-        v[r] = cmul(U[r], chirp(fmaf(-A, g, bse)));
+        return chirp(fmaf(-A, g, bse));
+      };
+#pragma unroll
+      for (int n = 0; n < 8; ++n) {
+        v[n] = cmul(U[n], factor(n));
+        v[n + 8] = U[n + 8];
+        bf2(v[n], v[n + 8], factor(n + 8));
       }
-      __syncthreads();  // previous trial's last LDS reads are done
-      fft4096<true, true>(v, lds, tws, jo);
+      fft4096<true, true, true>(v, lds, tws, pass2_twiddle, jo);
       float2 *out = outb + jt * trial_stride;
 #pragma unroll
       for (int r = 8; r < 16; ++r) out[256 * (r - 8)] = v[r];
     }
+  }
+}
+
+// The same with one trial: a workgroup walks a run of hops of one series.
+// The next hop's samples are read while this one is transformed, and the half
+// that it shares with this one is kept instead of read again (61 beams x 244
+// subbands x 16 hops: 2476 -> 2365 us, 3.3 TB/s).  What bounds both kernels is
+// the latency between the barriers, four waves per SIMD issuing an instruction
+// per 4 cycles where 2.1 would do; tried and slower: one wave per hop with 64
+// points per lane and one exchange without barriers (two waves per SIMD, 2972
+// us), and an unpadded tile for five workgroups per CU (spills at 96
+// registers).
+__global__ __launch_bounds__(kDdThreads)
+__attribute__((amdgpu_waves_per_eu(4, 8))) void dd_single_kernel(
+    const float2 *__restrict__ y, float2 *__restrict__ tail, int update_tail,
+    float2 *__restrict__ d, const float2 *__restrict__ tw,
+    const float *__restrict__ base, const float *__restrict__ afac,
+    const float *__restrict__ gq, int n_sb, long n_t, int n_hop, int per_wg,
+    int runs, long n_blocks) {
+  __shared__ float2 lds[kDdLds];
+  __shared__ DdTw tws;
+  const int j = threadIdx.x;
+  const long bid = xcd_remap(blockIdx.x, n_blocks);
+  const int h0 = (int)(bid % runs) * per_wg;
+  const int h1 = min(h0 + per_wg, n_hop);
+  const long bs = bid / runs;  // beam * n_sb + subband
+  const int s = (int)(bs % n_sb);
+  const float2 *ys = y + bs * n_t + j;
+  float2 *tl = tail + bs * kHist + j;
+  float2 *out = d + bs * n_t + j;
+
+  float2 last[8], next[8];
+#pragma unroll
+  for (int r = 0; r < 8; ++r)
+    last[r] = h0 == 0 ? tl[256 * r] : ys[(long)(h0 - 1) * kHop + 256 * r];
+#pragma unroll
+  for (int r = 0; r < 8; ++r) next[r] = ys[(long)h0 * kHop + 256 * r];
+  if (j < 16) {  // tw[n] = w^n, n < 4096
+    const int i = 16 * j;
+    tws.p1[j] = {tw[i], tw[2 * i], tw[4 * i], tw[8 * i]};
+  }
+  // (the barrier inside the first transform orders these before use)
+  const Tw16 w2p = {tw[j], tw[2 * j], tw[4 * j], tw[8 * j]};
+  auto pass2_twiddle = [&](int) { return w2p; };
+  const __amdgpu_buffer_rsrc_t grs = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<float *>(gq), 0, n_sb * kNfft * 4, kRawBufferWord3);
+  const float bse = fold_phase(base[s], 0.25f * (float)(j & 3)), A = afac[s];
+  // This thread read its part of the old tail above: the new one can go there.
+  if (update_tail && h0 == 0) {
+#pragma unroll
+    for (int r = 0; r < 8; ++r) tl[256 * r] = ys[n_t - kHist + 256 * r];
+  }
+  for (int h = h0; h < h1; ++h) {
+    const int jo = opaque(j);
+    float2 v[16];
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      v[r] = last[r];
+      v[8 + r] = last[r] = next[r];
+    }
+    if (h + 1 < h1) {
+#pragma unroll
+      for (int r = 0; r < 8; ++r) next[r] = ys[(long)(h + 1) * kHop + 256 * r];
+    }
+    fft4096<false, false, false>(v, lds, tws, pass2_twiddle, jo);
+    const int goff = 4 * (s * kNfft + jo);
+    auto factor = [&](int r) {
+      const float g = __uint_as_float(
+          __builtin_amdgcn_raw_buffer_load_b32(grs, goff, 1024 * r, 0));
+      return chirp(fmaf(-A, g, bse));
+    };
+    auto scaled = [&](int r) {
+      return make_float2(v[r].x * (1.0f / 4096.0f), v[r].y * (1.0f / 4096.0f));
+    };
+#pragma unroll
+    for (int n = 0; n < 8; ++n) {
+      v[n] = cmul(scaled(n), factor(n));
+      v[n + 8] = scaled(n + 8);
+      bf2(v[n], v[n + 8], factor(n + 8));
+    }
+    fft4096<true, true, true>(v, lds, tws, pass2_twiddle, jo);
+#pragma unroll
+    for (int r = 8; r < 16; ++r) out[(long)h * kHop + 256 * (r - 8)] = v[r];
   }
 }
 
@@ -300,6 +355,24 @@ lp_status dd_launch(lp_ctx *ctx, DdPlan *p, int n_sb, const void *y,
     return set_error(LP_EINVAL, "de-dispersion: trials %d..%d of %d", j0,
                      j0 + nj - 1, p->n_tec);
   const size_t jo = (size_t)j0 * n_sb;
+  // One trial and many hops: runs of hops, each workgroup's long enough that
+  // the samples read ahead pay for the start, with sixteen workgroups per CU
+  // so that the last ones cost little.  Shorter runs lose: 244 series of 32
+  // hops took 81 us in runs of 2 against 77 us hop by hop.
+  const int per_wg = (int)std::min<long>(n_hop, nb / (16L * ctx->n_cu));
+  if (nj == 1 && per_wg >= 4) {
+    const int runs = (n_hop + per_wg - 1) / per_wg;
+    const long n_wg = (long)n_beams * n_sb * runs;
+    hipLaunchKernelGGL(dd_single_kernel, dim3((unsigned)n_wg),
+                       dim3(kDdThreads), 0, st, static_cast<const float2 *>(y),
+                       static_cast<float2 *>(tail), update_tail ? 1 : 0,
+                       static_cast<float2 *>(d), ctx->tw4096.as<const float2>(),
+                       p->base.as<const float>() + jo,
+                       p->afac.as<const float>() + jo, p->gq.as<const float>(),
+                       n_sb, n_t, n_hop, per_wg, runs, n_wg);
+    LP_HIP(hipGetLastError());
+    return LP_OK;
+  }
   auto kern = p->uniform && nj >= 2 ? dd_kernel<true> : dd_kernel<false>;
   hipLaunchKernelGGL(kern, dim3((unsigned)nb), dim3(kDdThreads), 0, st,
                      static_cast<const float2 *>(y), static_cast<float2 *>(tail),

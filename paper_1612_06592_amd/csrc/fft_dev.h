@@ -149,6 +149,180 @@ __device__ __forceinline__ void dft16(float2 *v) {
     for (int k2 = 0; k2 < 4; ++k2) v[k1 + 4 * k2] = t[4 * k1 + k2];
 }
 
+// Radix-2 butterflies in fused multiply-adds: (a, b) <- (a + w b, a - w b).
+// The sum takes two FMAs per component and the difference is 2 a minus the
+// sum, one more: 6 instructions with the twiddle's product in them, where a
+// complex product and two sums take 8.  A DFT built of these (decimation in
+// time) needs no products by its external twiddles: input r is to be
+// multiplied by w^r, and w^8, w^4, w^2 and w go into the four stages.
+__device__ __forceinline__ void bf2(float2 &a, float2 &b, float2 w) {
+  const float x = fmaf(w.x, b.x, fmaf(-w.y, b.y, a.x));
+  const float y = fmaf(w.x, b.y, fmaf(w.y, b.x, a.y));
+  b = make_float2(fmaf(2.f, a.x, -x), fmaf(2.f, a.y, -y));
+  a = make_float2(x, y);
+}
+// a - w b alone (b takes it).
+__device__ __forceinline__ void bf2_diff(float2 a, float2 &b, float2 w) {
+  b = make_float2(fmaf(-w.x, b.x, fmaf(w.y, b.y, a.x)),
+                  fmaf(-w.x, b.y, fmaf(-w.y, b.x, a.y)));
+}
+// -i w (INV: +i w): the quarter-turn of a stage's twiddles.
+template <bool INV>
+__device__ __forceinline__ float2 quarter(float2 w) {
+  return INV ? make_float2(-w.y, w.x) : make_float2(w.y, -w.x);
+}
+// W8 w (INV: times its conjugate).
+template <bool INV>
+__device__ __forceinline__ float2 eighth(float2 w) {
+  constexpr float c = 0.70710678118654752f;
+  return INV ? make_float2(c * (w.x - w.y), c * (w.x + w.y))
+             : make_float2(c * (w.x + w.y), c * (w.y - w.x));
+}
+// The same butterflies for w = W16^m alone (m = 0..7), without its trivial
+// products.
+template <bool INV>
+__device__ __forceinline__ void bf2_w16(float2 &a, float2 &b, int m) {
+  const float2 p = a, q = b;
+  if (m == 0) {
+    a = cadd(p, q);
+    b = csub(p, q);
+  } else if (m == 4) {
+    const float2 iq = quarter<INV>(q);
+    a = cadd(p, iq);
+    b = csub(p, iq);
+  } else if (m == 2 || m == 6) {  // c (s, d) or c (d', -s') of the sums
+    constexpr float c = 0.70710678118654752f;
+    const float s = q.x + q.y, d = q.y - q.x;
+    // W16^2 q = c (s, d), W16^6 q = c (d, -s); conjugated: c (-d, s) and
+    // c (-s, -d).
+    const float2 e = m == 2 ? (INV ? make_float2(-d, s) : make_float2(s, d))
+                            : (INV ? make_float2(-s, -d) : make_float2(d, -s));
+    a = make_float2(fmaf(c, e.x, p.x), fmaf(c, e.y, p.y));
+    b = make_float2(fmaf(-c, e.x, p.x), fmaf(-c, e.y, p.y));
+  } else {
+    const float2 w = w16(m);
+    bf2(a, b, INV ? make_float2(w.x, -w.y) : w);
+  }
+}
+
+// Stages 2 to 4 of the untwiddled 16-point DFT (stage 1, the pairs (n, n +
+// 8), done), natural order out.  NZ as in dft16_fma.
+template <bool INV, int NZ>
+__device__ __forceinline__ void dft16_tail(float2 *v) {
+#pragma unroll
+  for (int n = 0; n < 4; ++n) {
+    if (n + 4 < NZ) {
+      bf2_w16<INV>(v[n], v[n + 4], 0);
+      bf2_w16<INV>(v[n + 8], v[n + 12], 4);
+    } else {
+      v[n + 4] = v[n];
+      v[n + 12] = v[n + 8];
+    }
+  }
+#pragma unroll
+  for (int n = 0; n < 2; ++n) {
+    bf2_w16<INV>(v[n], v[n + 2], 0);
+    bf2_w16<INV>(v[n + 8], v[n + 10], 2);
+    bf2_w16<INV>(v[n + 4], v[n + 6], 4);
+    bf2_w16<INV>(v[n + 12], v[n + 14], 6);
+  }
+  float2 t[16];
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    // C_0[k], C_1[k] sit at the bit reversal of k (four bits, low one 0).
+    const int p = 8 * (k & 1) + 4 * ((k >> 1) & 1) + 2 * (k >> 2);
+    bf2_w16<INV>(v[p], v[p + 1], k);
+    t[k] = v[p];
+    t[k + 8] = v[p + 1];
+  }
+#pragma unroll
+  for (int i = 0; i < 16; ++i) v[i] = t[i];
+}
+
+// 16-point DFT in place, natural order in and out, of which only inputs 0 ..
+// NZ-1 can be nonzero (NZ 4..8 or 16; the others are not read).
+template <bool INV, int NZ = 16>
+__device__ __forceinline__ void dft16_fma(float2 *v) {
+#pragma unroll
+  for (int n = 0; n < 8; ++n) {
+    if (NZ == 16)
+      bf2_w16<INV>(v[n], v[n + 8], 0);
+    else
+      v[n + 8] = v[n];
+  }
+  dft16_tail<INV, NZ>(v);
+}
+
+// The external twiddle of a radix-16 butterfly: w and its powers 2, 4 and 8,
+// each rounded from the exact value (squaring w three times would take twelve
+// instructions and end eight times further off).
+struct Tw16 {
+  float2 w, w2, w4, w8;
+  template <bool CONJ>
+  __device__ __forceinline__ Tw16 conj_if() const {
+    if (!CONJ) return *this;
+    return {make_float2(w.x, -w.y), make_float2(w2.x, -w2.y),
+            make_float2(w4.x, -w4.y), make_float2(w8.x, -w8.y)};
+  }
+};
+
+// 16-point DFT of v[r] w^r (r = 0..15), natural order in and out; HI: only
+// outputs 8..15 are formed.  w is the twiddle as it multiplies (conjugated
+// by the caller for an inverse transform).
+template <bool INV, bool HI = false>
+__device__ __forceinline__ void dft16_twiddled(float2 *v, const Tw16 &tw) {
+  const float2 w = tw.w, w2 = tw.w2, w4 = tw.w4, w8 = tw.w8;
+#pragma unroll
+  for (int n = 0; n < 8; ++n) bf2(v[n], v[n + 8], w8);
+  const float2 w4q = quarter<INV>(w4);
+#pragma unroll
+  for (int n = 0; n < 4; ++n) {
+    bf2(v[n], v[n + 4], w4);
+    bf2(v[n + 8], v[n + 12], w4q);
+  }
+  const float2 w2e = eighth<INV>(w2), w2q = quarter<INV>(w2),
+               w2s = quarter<INV>(w2e);
+#pragma unroll
+  for (int n = 0; n < 2; ++n) {
+    bf2(v[n], v[n + 2], w2);
+    bf2(v[n + 8], v[n + 10], w2e);
+    bf2(v[n + 4], v[n + 6], w2q);
+    bf2(v[n + 12], v[n + 14], w2s);
+  }
+  float2 t[16], wk[8];
+  wk[0] = w;
+  wk[1] = INV ? cmulc(w, w16(1)) : cmul(w, w16(1));
+  wk[2] = eighth<INV>(w);
+  wk[3] = INV ? cmulc(w, w16(3)) : cmul(w, w16(3));
+#pragma unroll
+  for (int k = 0; k < 4; ++k) wk[k + 4] = quarter<INV>(wk[k]);
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    const int p = 8 * (k & 1) + 4 * ((k >> 1) & 1) + 2 * (k >> 2);
+    if (HI)
+      bf2_diff(v[p], v[p + 1], wk[k]);
+    else
+      bf2(v[p], v[p + 1], wk[k]);
+    t[k] = v[p];
+    t[k + 8] = v[p + 1];
+  }
+#pragma unroll
+  for (int i = HI ? 8 : 0; i < 16; ++i) v[i] = t[i];
+}
+
+// 4-point DFT of (a, b w, c w^2, d w^3), w2 = w^2.
+template <bool INV>
+__device__ __forceinline__ void dft4_twiddled(float2 &a, float2 &b, float2 &c,
+                                              float2 &d, float2 w, float2 w2) {
+  bf2(a, c, w2);
+  bf2(b, d, w2);
+  bf2(a, b, w);                // outputs 0, 2
+  bf2(c, d, quarter<INV>(w));  // outputs 1, 3
+  const float2 t = b;
+  b = c;
+  c = t;
+}
+
 // Twiddle from the 4096-entry table exp(-2 pi i n / 4096); INV conjugates.
 template <bool INV>
 __device__ __forceinline__ float2 twiddle(const float2 *__restrict__ tw,
