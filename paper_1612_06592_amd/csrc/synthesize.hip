@@ -15,12 +15,23 @@
 // exchanges between passes stay inside the wave (through LDS after pass 0,
 // by lane swaps across rows of 16 after pass 1) and a chunk needs two
 // workgroup barriers (transforms done; FIR done).  Thread n then owns FIR
-// column n and keeps
-// Z_{m-15..m}[n] and its 16 taps in registers, so each output sample costs
-// 16 complex-by-real FMAs and nothing is written to HBM except the
-// per-frame envelope maximum (+ arg), per-16-frame sums of (2 Re z)^2 and,
-// on request, the real series.
+// column n and keeps Z_{m-15..m}[n] and its 16 taps in registers, so each
+// output sample costs 16 complex-by-real FMAs and nothing is written to HBM
+// except the per-frame envelope maximum (+ arg), per-16-frame sums of
+// (2 Re z)^2 and, on request, the real series.
+//
+// What bounds it is the vector ALU between those barriers: of ~17100 cycles
+// per chunk and CU, ~1150 instructions on each of a SIMD's four waves need
+// ~9700 at the paired rate.  Alone, 61 series x 244 subbands x 32768 frames:
+// 4160 -> 3446 us, by taps that stay in registers (they were read again every
+// chunk, after the barrier), FIR sums in eight independent chains, a store of
+// the series that is no branch where it is not asked for, butterflies in FMA
+// form, and the next inputs requested before the barrier.  Tried and slower:
+// envelope maxima in registers with the two barriers side by side (3944 to
+// 4359 us), pass 0 of the next chunk under the arg-max reads (3741), the
+// square roots of a chunk by one wave (3667).
 #include <cmath>
+#include <type_traits>
 
 #include "fft_dev.h"
 #include "lp_internal.h"
@@ -86,8 +97,9 @@ __device__ __forceinline__ unsigned wave_umax_dpp(unsigned v) {
 // a multiple of 16), so the statistics mask frame by frame; otherwise a
 // chunk is either all warm-up or all valid.  NR: bins j + 64 r with r >= NR
 // are empty in the band (its highest bin is below 64 NR), so the first
-// transform pass reads NR inputs and the rest are known zeros.
-template <bool MASKED, int NR>
+// transform pass reads NR inputs and the rest are known zeros.  SERIES: the
+// real series is written too.
+template <bool MASKED, int NR, bool SERIES>
 __global__ __launch_bounds__(kSynThreads) void syn_kernel(
     const float2 *__restrict__ d, float2 *__restrict__ hist,
     const short *__restrict__ binmap, const float *__restrict__ taps,
@@ -96,13 +108,12 @@ __global__ __launch_bounds__(kSynThreads) void syn_kernel(
     long frame0, long warm, long per_wg, long total, long cand_nt,
     long cand_t0) {
   __shared__ float2 lds[16 * kSynFs];
-  // Base twiddles of the two twiddled passes; each lane forms the powers it
-  // needs by products (reading every power from LDS tables was 4 % slower:
-  // the transform is bound by the latency of its LDS accesses):
-  //   tw_p1[a] = exp(+2 pi i 4 a / 1024)   (pass 1, a = j mod 16)
-  //   tw_p2[t] = exp(+2 pi i t / 1024)     (pass 2, t < 256)
-  __shared__ float2 tw_p1[16];
-  __shared__ float2 tw_p2[256];
+  // Twiddles of the two twiddled passes (w = exp(+2 pi i / 1024)), with the
+  // powers that the butterflies take:
+  //   tw_p1[a]: powers 1, 2, 4, 8 of w^(4 a)   (pass 1, a = j mod 16)
+  //   tw_p2[t]: w^t and w^(2 t)                (pass 2, t < 256)
+  __shared__ Tw16 tw_p1[16];
+  __shared__ float4 tw_p2[256];
   __shared__ float red_s[16];
   // Byte offset in the series of the row of bin j + 64 r (lane j), or the
   // series size for an empty bin (a raw buffer load past the end reads 0).
@@ -115,11 +126,14 @@ __global__ __launch_bounds__(kSynThreads) void syn_kernel(
   float2 win[16];
 #pragma unroll
   for (int t = 0; t < 16; ++t) win[t] = make_float2(0.f, 0.f);
-  if (tid < 256 + 16) {
-    // From the table exp(-2 pi i n / 4096), conjugated.
-    const int t = tid < 256 ? tid : 4 * (tid - 256);
-    const float2 w = tw[4 * t];
-    (tid < 256 ? tw_p2[tid] : tw_p1[tid - 256]) = make_float2(w.x, -w.y);
+  // From the table exp(-2 pi i n / 4096), conjugated.
+  if (tid < 256) {
+    const float2 w = tw[4 * tid], w2 = tw[8 * tid];
+    tw_p2[tid] = make_float4(w.x, -w.y, w2.x, -w2.y);
+  } else if (tid < 256 + 16) {
+    const int i = 16 * (tid - 256);
+    tw_p1[tid - 256] =
+        Tw16{tw[i], tw[2 * i], tw[4 * i], tw[8 * i]}.conj_if<true>();
   }
   // Wave w transforms frame w of each 16-frame chunk; lane j is pass-0
   // butterfly j, reading bins j + 64 r (r < NR) at the offsets in roff_s.
@@ -130,16 +144,21 @@ __global__ __launch_bounds__(kSynThreads) void syn_kernel(
   }
   __syncthreads();
 
+  // Taps (2 g) of column n, for the life of the workgroup.
+  float g[16];
+#pragma unroll
+  for (int t = 0; t < 16; ++t) g[t] = taps[1024 * t + n];
+
   // This workgroup's frames: [g, g_end) of the series-major frame index
   // series * n_t + m, as segments of one series each (every segment starts
   // with its own 16-frame warm-up chunk).
-  long g = (long)blockIdx.x * per_wg;
-  const long g_end = min(g + per_wg, total);
-  for (; g < g_end;) {
-    const int series = (int)(g / n_t);
-    const long m0 = g - (long)series * n_t;
-    const long seg = min(g_end - g, n_t - m0);
-    g += seg;
+  long gi = (long)blockIdx.x * per_wg;
+  const long g_end = min(gi + per_wg, total);
+  for (; gi < g_end;) {
+    const int series = (int)(gi / n_t);
+    const long m0 = gi - (long)series * n_t;
+    const long seg = min(g_end - gi, n_t - m0);
+    gi += seg;
     const float2 *ds = d + (long)series * n_sb * n_t;
     float2 *hs = hist + (long)series * n_sb * kSynHist;
     const __amdgpu_buffer_rsrc_t drs = __builtin_amdgcn_make_buffer_rsrc(
@@ -147,27 +166,26 @@ __global__ __launch_bounds__(kSynThreads) void syn_kernel(
     const int n_chunk = (int)(seg / 16);
     float2 pre[NR];
     auto fetch = [&](long mc_) {
-      const long m = mc_ + wave;
-      if (m >= 0) {
-        typedef unsigned u2 __attribute__((ext_vector_type(2)));
-        const unsigned mo = (unsigned)m * 8u;
+      typedef unsigned u2 __attribute__((ext_vector_type(2)));
+      const unsigned mo = (unsigned)(mc_ + wave) * 8u;
 #pragma unroll
-        for (int r = 0; r < NR; ++r) {
-          const u2 b = __builtin_amdgcn_raw_buffer_load_b64(
-              drs, roff_s[64 * r + lane] + mo, 0, 0);
-          pre[r] = make_float2(__uint_as_float(b.x), __uint_as_float(b.y));
-        }
-      } else {
-        // Before the stream block (warm-up chunk of workgroup 0): history.
-#pragma unroll
-        for (int r = 0; r < NR; ++r) {
-          const int si = binmap[lane + 64 * r];
-          pre[r] = si >= 0 ? hs[si * kSynHist + (kSynHist + m)]
-                           : make_float2(0.f, 0.f);
-        }
+      for (int r = 0; r < NR; ++r) {
+        const u2 b = __builtin_amdgcn_raw_buffer_load_b64(
+            drs, roff_s[64 * r + lane] + mo, 0, 0);
+        pre[r] = make_float2(__uint_as_float(b.x), __uint_as_float(b.y));
       }
     };
-    fetch(m0 - 16);
+    if (m0 == 0) {
+      // The block's first warm-up chunk comes from the history.
+      const int ln = opaque(lane), wv = opaque(wave);
+#pragma unroll
+      for (int r = 0; r < NR; ++r) {
+        const int si = binmap[ln + 64 * r];
+        pre[r] = si >= 0 ? hs[si * kSynHist + wv] : make_float2(0.f, 0.f);
+      }
+    } else {
+      fetch(m0 - 16);
+    }
     for (int c = -1; c < n_chunk; ++c) {
       const long mc = m0 + 16L * c;  // first frame of the chunk
       const int no = opaque(n), lo = opaque(lane), wo = opaque(wave);
@@ -179,9 +197,7 @@ __global__ __launch_bounds__(kSynThreads) void syn_kernel(
       float2 v[16];
 #pragma unroll
       for (int r = 0; r < NR; ++r) v[r] = pre[r];
-#pragma unroll
-      for (int r = NR; r < 16; ++r) v[r] = make_float2(0.f, 0.f);
-      dft16<true, NR>(v);
+      dft16_fma<true, NR>(v);
       // pad16(16 j + r) = 17 j + r.
 #pragma unroll
       for (int r = 0; r < 16; ++r) fr[17 * lo + r] = v[r];
@@ -194,29 +210,8 @@ __global__ __launch_bounds__(kSynThreads) void syn_kernel(
         // ---- pass 1 (radix 16, Ns = 16).
 #pragma unroll
         for (int r = 0; r < 16; ++r) v[r] = fr[b1 + 68 * r];
-        {
-          // v[r] *= w^r, w = exp(2 pi i (j mod 16) / 256): a product tree
-          // of depth 4, each power used as soon as it exists.
-          const float2 w1 = tw_p1[lo & 15];
-          const float2 w2 = cmul(w1, w1), w4 = cmul(w2, w2), w8 = cmul(w4, w4);
-          const float2 w3 = cmul(w2, w1), w7 = cmul(w4, w3);
-          v[1] = cmul(v[1], w1);
-          v[2] = cmul(v[2], w2);
-          v[3] = cmul(v[3], w3);
-          v[4] = cmul(v[4], w4);
-          v[5] = cmul(v[5], cmul(w4, w1));
-          v[6] = cmul(v[6], cmul(w4, w2));
-          v[7] = cmul(v[7], w7);
-          v[8] = cmul(v[8], w8);
-          v[9] = cmul(v[9], cmul(w8, w1));
-          v[10] = cmul(v[10], cmul(w8, w2));
-          v[11] = cmul(v[11], cmul(w8, w3));
-          v[12] = cmul(v[12], cmul(w8, w4));
-          v[13] = cmul(v[13], cmul(w8, cmul(w4, w1)));
-          v[14] = cmul(v[14], cmul(w8, cmul(w4, w2)));
-          v[15] = cmul(v[15], cmul(w8, w7));
-        }
-        dft16<true>(v);
+        // v[r] w^r, w = exp(2 pi i (j mod 16) / 256), in the butterflies.
+        dft16_twiddled<true>(v, tw_p1[lo & 15]);
         pass2_gather(v);  // v[4 q + m] = element j + 64 q + 256 m
         // ---- pass 2 (radix 4, Ns = 256): butterflies j + 64 q, q < 4,
         // written to their output slots
@@ -227,38 +222,26 @@ __global__ __launch_bounds__(kSynThreads) void syn_kernel(
           float2 *sl = fr + b1 + 68 * q;
           float2 a0 = v[4 * q], a1 = v[4 * q + 1], a2 = v[4 * q + 2],
                  a3 = v[4 * q + 3];
-          const float2 u1 = tw_p2[jt], u2 = cmul(u1, u1), u3 = cmul(u2, u1);
-          a1 = cmul(a1, u1);
-          a2 = cmul(a2, u2);
-          a3 = cmul(a3, u3);
-          dft4<true>(a0, a1, a2, a3);
+          const float4 u = tw_p2[jt];
+          dft4_twiddled<true>(a0, a1, a2, a3, make_float2(u.x, u.y),
+                              make_float2(u.z, u.w));
           sl[0] = a0;
           sl[272] = a1;
           sl[544] = a2;
           sl[816] = a3;
         }
       }
-      // Taps (2 g) of column n, in flight across the barrier.  A raw buffer
-      // view of the 16 x 1024 taps: tap t of column n is at the constant
-      // offset 4096 t plus 4 n.
-      const __amdgpu_buffer_rsrc_t trs = __builtin_amdgcn_make_buffer_rsrc(
-          const_cast<float *>(taps), 0, 16 * 1024 * 4, kRawBufferWord3);
-      float g[16];
-#pragma unroll
-      for (int t = 0; t < 16; ++t)
-        g[t] = __uint_as_float(
-            __builtin_amdgcn_raw_buffer_load_b32(trs, 4 * no, 4096 * t, 0));
+      // Next chunk's inputs are in flight meanwhile.
+      if (c + 1 < n_chunk) fetch(mc + 16);
       __syncthreads();  // every frame of the chunk is transformed
       if (c == -1 && m0 == 0) {
         // Every history read of this block happened above: store the new
         // history, the last 16 frames of d.
-        for (int i = tid; i < n_sb * kSynHist; i += kSynThreads) {
+        for (int i = no; i < n_sb * kSynHist; i += kSynThreads) {
           int si = i / kSynHist, fi = i % kSynHist;
           hs[i] = ds[(long)si * n_t + (n_t - kSynHist + fi)];
         }
       }
-      // Next chunk's inputs are in flight while this chunk is filtered.
-      if (c + 1 < n_chunk) fetch(mc + 16);
       // ---- FIR, envelope, statistics for the 16 frames of this chunk.
       if (c < 0) {
 #pragma unroll
@@ -270,26 +253,44 @@ __global__ __launch_bounds__(kSynThreads) void syn_kernel(
       // Frames before `warm` (stream time) stay out of the statistics.
       const long fv = warm - (frame0 + mc);
       const int first_valid = fv <= 0 ? 0 : (fv >= 16 ? 16 : (int)fv);
-      float *xo = x_out ? x_out + ((long)series * n_t + mc) * 1024 + no : nullptr;
+      float *xo = SERIES ? x_out + ((long)series * n_t + mc) * 1024 + no : nullptr;
       // (zr, zi) = 2 z of frame fi: 2 Re z is the real series, |2 z|^2 the
       // squared envelope; the slot is consumed, so it takes the latter, in
       // its x word for columns with bit 4 clear and its y word otherwise (the
       // 16-column groups then alternate between even and odd banks).
       const int ecomp = (no >> 4) & 1;
+      // Four frames at a time: their eight sums are independent chains (one
+      // chain alone would wait for each FMA), and the next four frames are
+      // read meanwhile.
+      float2 *const col = lds + pad16(no);
+      float2 nw[2][4];
 #pragma unroll
-      for (int fi = 0; fi < 16; ++fi) {
-        float2 *slot = lds + fi * kSynFs + pad16(no);
-        win[fi] = *slot;
-        float zr = 0.f, zi = 0.f;
+      for (int i = 0; i < 4; ++i) nw[0][i] = col[i * kSynFs];
 #pragma unroll
-        for (int t = 0; t < 16; ++t) {
-          float2 w = win[(fi - t) & 15];
-          zr = fmaf(g[t], w.x, zr);
-          zi = fmaf(g[t], w.y, zi);
+      for (int f0 = 0; f0 < 16; f0 += 4) {
+        float2 *const cur = nw[(f0 >> 2) & 1], *const nxt = nw[(~f0 >> 2) & 1];
+        if (f0 < 12) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) nxt[i] = col[(f0 + 4 + i) * kSynFs];
         }
-        if (!MASKED || fi >= first_valid) acc_s = fmaf(zr, zr, acc_s);
-        if (xo) xo[(long)fi * 1024] = zr;
-        reinterpret_cast<float *>(slot)[ecomp] = zr * zr + zi * zi;
+        float zr[4] = {0.f, 0.f, 0.f, 0.f}, zi[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int t = 0; t < 16; ++t)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const float2 w = i >= t ? cur[i - t] : win[(f0 + i - t) & 15];
+            zr[i] = fmaf(g[t], w.x, zr[i]);
+            zi[i] = fmaf(g[t], w.y, zi[i]);
+          }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int fi = f0 + i;
+          win[fi] = cur[i];
+          if (!MASKED || fi >= first_valid) acc_s = fmaf(zr[i], zr[i], acc_s);
+          if (SERIES) xo[(long)fi * 1024] = zr[i];
+          reinterpret_cast<float *>(col + fi * kSynFs)[ecomp] =
+              zr[i] * zr[i] + zi[i] * zi[i];
+        }
       }
       if (!MASKED && first_valid != 0) acc_s = 0.f;  // first_valid is 16
       acc_s = wave_sum_dpp(acc_s);
@@ -414,15 +415,20 @@ lp_status syn_launch(lp_ctx *ctx, SynPlan *p, int n_sb, const void *d,
   float *ps = reinterpret_cast<float *>(cb + (size_t)n_series_total * cand_nt * 8) +
               (size_t)series0 * (cand_nt / 16);
   // Kernel for the band's highest bin: pass-0 rows 4, 5, 6 or 8.
-  decltype(&syn_kernel<false, 8>) kern;
+  decltype(&syn_kernel<false, 8, false>) kern;
+  auto pick = [&](auto nr_c) {
+    constexpr int R = decltype(nr_c)::value;
+    kern = x_out ? (masked ? syn_kernel<true, R, true> : syn_kernel<false, R, true>)
+                 : (masked ? syn_kernel<true, R, false> : syn_kernel<false, R, false>);
+  };
   if (p->kmax < 256)
-    kern = masked ? syn_kernel<true, 4> : syn_kernel<false, 4>;
+    pick(std::integral_constant<int, 4>());
   else if (p->kmax < 320)
-    kern = masked ? syn_kernel<true, 5> : syn_kernel<false, 5>;
+    pick(std::integral_constant<int, 5>());
   else if (p->kmax < 384)
-    kern = masked ? syn_kernel<true, 6> : syn_kernel<false, 6>;
+    pick(std::integral_constant<int, 6>());
   else
-    kern = masked ? syn_kernel<true, 8> : syn_kernel<false, 8>;
+    pick(std::integral_constant<int, 8>());
   hipLaunchKernelGGL(kern, dim3((unsigned)n_wg), dim3(kSynThreads), 0, st,
                      static_cast<const float2 *>(d),
                      static_cast<float2 *>(hist), p->binmap.as<const short>(),
