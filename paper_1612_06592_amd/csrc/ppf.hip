@@ -12,7 +12,7 @@
 //   W_m[r]  = Re sum_s y_s[m] exp(-2 pi i k[s] r / 1024)
 //   (H^T y)[1024 j + 1023 - r] = sum_{t<16} h[1024 t + r] W_{j + t}[r].
 //
-// Kernels.  Both operators stream 256 frames per 1024-thread workgroup in
+// Kernels.  Both operators stream a run of frames per 1024-thread workgroup in
 // chunks of 32 real frames, packed two per complex 1024-point transform
 // (16 transforms per chunk in a 139 KB LDS tile, Stockham radix 16, 16,
 // 4, wave w transforming packed frame w).  Thread r owns FIR column r and
@@ -38,7 +38,6 @@ namespace lp {
 
 constexpr int kPpfThreads = 1024;
 constexpr int kPpfFs = 1090;       // LDS stride of one packed frame (float2)
-constexpr int kPpfWg = 256;        // frames per workgroup
 constexpr int kPpfChunk = 32;      // real frames per chunk
 constexpr int kPpfNormParts = 2048; // partial sums of ||y||^2 per series
 constexpr int kPpfStateBytes = 128;
@@ -179,14 +178,14 @@ __global__ __launch_bounds__(kPpfThreads) void ppf_fwd_kernel(
     float *__restrict__ hv, float *__restrict__ hbar, float *__restrict__ xv,
     const LsmrState *__restrict__ st, float *__restrict__ part,
     const short *__restrict__ kbin, const float *__restrict__ taps,
-    const float2 *__restrict__ tw, int n_sb, long nf, int n_part,
+    const float2 *__restrict__ tw, int n_sb, long nf, int per_wg, int n_part,
     float oscale = 1.f, int olim = 0, short2 *__restrict__ sout = nullptr) {
   __shared__ float2 lds[16 * kPpfFs];
   __shared__ float2 tw_p1[kTwP1], tw_p2[kTwP2];
   __shared__ float red[16];
 
   const int series = blockIdx.y;
-  const long m0 = (long)blockIdx.x * kPpfWg;
+  const long m0 = (long)blockIdx.x * per_wg;
   const long F = nf - (kTaps - 1);
   const long N = F * kM;
   const int tid = threadIdx.x;
@@ -241,9 +240,8 @@ __global__ __launch_bounds__(kPpfThreads) void ppf_fwd_kernel(
   for (int i = 1; i < 16; ++i)  // frames m0 - 15 .. m0 - 1 (zero if < 0)
     ring[i] = ldx((int)(m0 - 16 + i) * kM + (kM - 1 - tid)) * sc;
   float acc = 0.f;
-  for (int c = 0; c < kPpfWg / kPpfChunk; ++c) {
-    const long mc = m0 + (long)c * kPpfChunk;
-    if (mc >= nf) break;
+  const long m1 = min(m0 + per_wg, nf);
+  for (long mc = m0; mc < m1; mc += kPpfChunk) {
     const int ro = opaque(tid);
     const int lo = opaque(tid & 63), wo = opaque(tid >> 6);
     float g[16];
@@ -373,7 +371,8 @@ __global__ __launch_bounds__(kPpfThreads) void ppf_adj_kernel(
     const float2 *__restrict__ yin, float *pio,
     const LsmrState *__restrict__ st, float *__restrict__ part,
     const short *__restrict__ binmap, const float *__restrict__ taps,
-    const float2 *__restrict__ tw, int n_sb, long nf, int n_part) {
+    const float2 *__restrict__ tw, int n_sb, long nf, int per_wg,
+    int n_part) {
   __shared__ float2 lds[16 * kPpfFs];
   __shared__ float2 tw_p1[kTwP1], tw_p2[kTwP2];
   __shared__ float red[16];
@@ -385,8 +384,8 @@ __global__ __launch_bounds__(kPpfThreads) void ppf_adj_kernel(
   const int series = blockIdx.y;
   const long F = nf - (kTaps - 1);
   const long N = F * kM;
-  const long j0 = (long)blockIdx.x * kPpfWg;
-  const long jend = min(j0 + (long)kPpfWg, F);
+  const long j0 = (long)blockIdx.x * per_wg;
+  const long jend = min(j0 + (long)per_wg, F);
   const long wend = jend + (kTaps - 1);  // W frames [j0, wend) are used
   const int tid = threadIdx.x;
   const int f = tid & 15, j = tid >> 4;
@@ -747,9 +746,50 @@ __global__ __launch_bounds__(256) void station_transpose_vec_kernel(
 
 // ------------------------------------------------------------- host side
 
+// Frames per workgroup.  A workgroup is one CU's LDS tile and walks its frames
+// in chunks of 32: H's costs its frames / 32 and about half a chunk to start,
+// H^T's needs 15 frames past its own (32 i - 16 frames fill i chunks).  Runs of
+// 256 frames are right where they fill the chip for several rounds (longer
+// ones, filling it once, measured 2-3 % slower: a slow CU then holds up the
+// whole launch, which the 10 % stands for).  Where 256 would leave CUs idle or
+// a second round nearly empty, the run that fills the chip once or twice is
+// taken: one series of 32768 frames 533 -> 345 us an LSMR iteration, of 2048
+// frames 291 -> 61 us.  Lengths stay even (H: multiples of 32), so the frame
+// pairs that share a transform, and with them every output bit, do not depend
+// on them.
+struct PpfRuns {
+  int per_wg = 0, n_wg = 0;
+};
+static PpfRuns ppf_runs(int n_cu, int n_series, long frames, bool adj) {
+  const long most = std::min<long>(kPpfNormParts, (frames + 31) / 32);
+  PpfRuns best;
+  double cost = 0.0;
+  auto consider = [&](long chunks) {
+    const long w = adj ? 32 * chunks - 16 : 32 * chunks;
+    const long n = (frames + w - 1) / w;
+    if (n > kPpfNormParts) return;
+    const double r = (double)n * n_series / n_cu;
+    const double rounds = r <= 3.0 ? std::ceil(r) : r + 0.5;
+    const double c = rounds * (chunks + (adj ? 0.0 : 0.5)) *
+                     (chunks > (adj ? 9 : 8) ? 1.1 : 1.0);
+    if (best.n_wg == 0 || c < cost) {
+      cost = c;
+      best = {(int)w, (int)n};
+    }
+  };
+  consider(adj ? 9 : 8);
+  for (int rounds = 1; rounds <= 3; ++rounds) {
+    const long want =
+        std::min(std::max<long>((long)rounds * n_cu / n_series, 1), most);
+    const long per = (frames + want - 1) / want;
+    consider(adj ? (per + 16 + 31) / 32 : (per + 31) / 32);
+  }
+  return best;
+}
+
 struct PpfLayout {
   long F = 0, N = 0;
-  int n_fwd = 0, n_adj = 0, n_part = 0;
+  int n_part = 0;
   size_t st = 0, part = 0, q = 0, p = 0, h = 0, hbar = 0, total = 0;
 };
 
@@ -759,9 +799,9 @@ static PpfLayout ppf_layout(int n_sb, int n_series, long nf) {
   PpfLayout L;
   L.F = nf - (kTaps - 1);
   L.N = L.F * kM;
-  L.n_fwd = (int)((nf + kPpfWg - 1) / kPpfWg);
-  L.n_adj = (int)((L.F + kPpfWg - 1) / kPpfWg);
-  L.n_part = std::max(std::max(L.n_fwd, L.n_adj), kPpfNormParts);
+  // (at most kPpfNormParts in use; a frame count past the operators' limit is
+  // sized all the same)
+  L.n_part = (int)std::max<long>((nf + 255) / 256, kPpfNormParts);
   size_t o = 0;
   L.st = o;
   o = align256(o + (size_t)n_series * kPpfStateBytes);
@@ -823,13 +863,13 @@ extern "C" lp_status lp_ppf_analyze(lp_ctx *ctx, const lp_band *band,
       (rc = plan_wait(p.get(), st)))
     return rc;
   const long nf = n_frames;
-  const int n_fwd = (int)((nf + kPpfWg - 1) / kPpfWg);
-  hipLaunchKernelGGL(ppf_fwd_kernel<kFwdAnalyze>, dim3(n_fwd, n_series),
+  const PpfRuns rf = ppf_runs(ctx->n_cu, n_series, nf, false);
+  hipLaunchKernelGGL(ppf_fwd_kernel<kFwdAnalyze>, dim3(rf.n_wg, n_series),
                      dim3(kPpfThreads), 0, st, x, (const float2 *)nullptr,
                      static_cast<float2 *>(y), nullptr, nullptr, nullptr,
                      nullptr, nullptr, p->kbin.as<const short>(),
                      p->taps.as<const float>(), ctx->tw4096.as<const float2>(),
-                     band->n_sb, nf, 0);
+                     band->n_sb, nf, rf.per_wg, 0);
   LP_HIP(hipGetLastError());
   return LP_OK;
 }
@@ -850,12 +890,13 @@ extern "C" lp_status lp_ppf_adjoint(lp_ctx *ctx, const lp_band *band,
       (rc = plan_wait(p.get(), st)))
     return rc;
   const long nf = n_frames, F = nf - (kTaps - 1);
-  const int n_adj = (int)((F + kPpfWg - 1) / kPpfWg);
-  hipLaunchKernelGGL(ppf_adj_kernel<kAdjPlain>, dim3(n_adj, n_series),
+  const PpfRuns ra = ppf_runs(ctx->n_cu, n_series, F, true);
+  hipLaunchKernelGGL(ppf_adj_kernel<kAdjPlain>, dim3(ra.n_wg, n_series),
                      dim3(kPpfThreads), 0, st,
                      static_cast<const float2 *>(y), x, nullptr, nullptr,
                      p->binmap.as<const short>(), p->taps.as<const float>(),
-                     ctx->tw4096.as<const float2>(), band->n_sb, nf, 0);
+                     ctx->tw4096.as<const float2>(), band->n_sb, nf, ra.per_wg,
+                     0);
   LP_HIP(hipGetLastError());
   return LP_OK;
 }
@@ -900,7 +941,9 @@ extern "C" lp_status lp_ppf_invert(lp_ctx *ctx, const lp_band *band,
   const float *taps = p->taps.as<const float>();
   const float2 *tw = ctx->tw4096.as<const float2>();
   const int an_stride = n_iter + 1;
-  const dim3 gf(L.n_fwd, n_series), ga(L.n_adj, n_series), blk(kPpfThreads);
+  const PpfRuns rf = ppf_runs(ctx->n_cu, n_series, nf, false),
+                ra = ppf_runs(ctx->n_cu, n_series, L.F, true);
+  const dim3 gf(rf.n_wg, n_series), ga(ra.n_wg, n_series), blk(kPpfThreads);
 
   // beta_1 u_1 = y; alpha_1 v_1 = H^T u_1.
   hipLaunchKernelGGL(ppf_sumsq_kernel, dim3(kPpfNormParts, n_series),
@@ -908,21 +951,21 @@ extern "C" lp_status lp_ppf_invert(lp_ctx *ctx, const lp_band *band,
   hipLaunchKernelGGL(lsmr_init_beta_kernel, dim3(n_series), dim3(64), 0, hs,
                      part, st);
   hipLaunchKernelGGL(ppf_adj_kernel<kAdjLsmr>, ga, blk, 0, hs, yv, pv, st,
-                     part, bmap, taps, tw, S, nf, L.n_adj);
+                     part, bmap, taps, tw, S, nf, ra.per_wg, ra.n_wg);
   hipLaunchKernelGGL(lsmr_init_alpha_kernel, dim3(n_series), dim3(64), 0, hs,
-                     part, L.n_adj, st, anorm, an_stride);
+                     part, ra.n_wg, st, anorm, an_stride);
   for (int k = 1; k <= n_iter; ++k) {
     // beta_{k+1} u_{k+1} = H v_k - alpha_k u_k (u_1 is y itself).
     hipLaunchKernelGGL(ppf_fwd_kernel<kFwdLsmr>, gf, blk, 0, hs, pv,
                        k == 1 ? yv : q, q, hv, hb, x, st, part, kbin, taps,
-                       tw, S, nf, L.n_fwd);
+                       tw, S, nf, rf.per_wg, rf.n_wg);
     hipLaunchKernelGGL(lsmr_beta_kernel, dim3(n_series), dim3(64), 0, hs,
-                       part, L.n_fwd, st);
+                       part, rf.n_wg, st);
     // alpha_{k+1} v_{k+1} = H^T u_{k+1} - beta_{k+1} v_k.
     hipLaunchKernelGGL(ppf_adj_kernel<kAdjLsmr>, ga, blk, 0, hs, q, pv, st,
-                       part, bmap, taps, tw, S, nf, L.n_adj);
+                       part, bmap, taps, tw, S, nf, ra.per_wg, ra.n_wg);
     hipLaunchKernelGGL(lsmr_alpha_kernel, dim3(n_series), dim3(64), 0, hs,
-                       part, L.n_adj, st, anorm, an_stride, k);
+                       part, ra.n_wg, st, anorm, an_stride, k);
   }
   hipLaunchKernelGGL(lsmr_final_kernel,
                      dim3((unsigned)((L.N + 255) / 256), n_series), dim3(256),
@@ -930,9 +973,9 @@ extern "C" lp_status lp_ppf_invert(lp_ctx *ctx, const lp_band *band,
   if (rnorm) {
     hipLaunchKernelGGL(ppf_fwd_kernel<kFwdResid>, gf, blk, 0, hs, x, yv,
                        (float2 *)nullptr, nullptr, nullptr, nullptr, st,
-                       part, kbin, taps, tw, S, nf, L.n_fwd);
+                       part, kbin, taps, tw, S, nf, rf.per_wg, rf.n_wg);
     hipLaunchKernelGGL(ppf_rnorm_kernel, dim3(n_series), dim3(64), 0, hs,
-                       part, L.n_fwd, rnorm);
+                       part, rf.n_wg, rnorm);
   }
   LP_HIP(hipGetLastError());
   return LP_OK;
@@ -975,14 +1018,14 @@ extern "C" lp_status lp_station_ppf(lp_ctx *ctx, const lp_band *band,
       (rc = plan_wait(p.get(), st)))
     return rc;
   const long nf = n_frames + 2 * (kTaps - 1);   // frames of H's output
-  const int n_fwd = (int)((nf + kPpfWg - 1) / kPpfWg);
+  const PpfRuns rf = ppf_runs(ctx->n_cu, n_in, nf, false);
   short2 *stage = static_cast<short2 *>(work);
-  hipLaunchKernelGGL(ppf_fwd_kernel<kFwdStation>, dim3(n_fwd, n_in),
+  hipLaunchKernelGGL(ppf_fwd_kernel<kFwdStation>, dim3(rf.n_wg, n_in),
                      dim3(kPpfThreads), 0, st, adc, (const float2 *)nullptr,
                      (float2 *)nullptr, nullptr, nullptr, nullptr, nullptr,
                      nullptr, p->kbin.as<const short>(),
                      p->taps.as<const float>(), ctx->tw4096.as<const float2>(),
-                     band->n_sb, nf, 0, scale, dtype == LP_CI8 ? 128 : 32768,
+                     band->n_sb, nf, rf.per_wg, 0, scale, dtype == LP_CI8 ? 128 : 32768,
                      stage);
   const long P = (long)band->n_sb * n_frames;
   const bool ci8 = dtype == LP_CI8;
