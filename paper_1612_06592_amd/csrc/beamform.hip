@@ -10,6 +10,7 @@
 // LP_FP32 does the same sums in FP32 with v_mfma_f32_16x16x4_f32.
 #include <cmath>
 #include <cstring>
+#include <initializer_list>
 #include <type_traits>
 
 #include "lp_internal.h"
@@ -196,9 +197,13 @@ __global__ __launch_bounds__(kBfThreads) void bf_mfma_kernel(
   // fragments of k-steps KS .. KSM-1 are zero too); they are zeroed once
   // (the tiles never write them), as are the scale factors past KS*16.
   // Every k-step then runs unconditionally.
-  const int padb = (KSM * 16 - RK) * (int)sizeof(IT);
-  for (int i = tid; i < T * padb; i += kBfThreads)
-    smb[(i / padb) * RSB + RK * (int)sizeof(IT) + (i % padb)] = 0;
+  // (A row and its padding are whole 32-bit words.)
+  const int padw = (KSM * 16 - RK) * (int)sizeof(IT) / 4;
+  for (int i = tid; i < T * padw; i += kBfThreads) {
+    const int row = i / padw;
+    *reinterpret_cast<unsigned *>(smb + row * RSB + RK * (int)sizeof(IT) +
+                                  4 * (i - row * padw)) = 0u;
+  }
   if (scaled)
     for (int i = tid; i < KSM * 16; i += kBfThreads)
       xs_lds[i] = i < KS * 16 ? xscale[i] : (_Float16)0.0f;
@@ -636,7 +641,10 @@ static lp_status launch_bf(const BfPlan *p, const void *x, long x_nt,
   const int vb = (row_bytes % 16 == 0) ? 16 : (row_bytes % 8 == 0) ? 8 : 4;
   if (p->prec == LP_FP16_MFMA) {
     const int NT = p->NT, KS = p->KS;
-    const int wn_shift = (NT == 1) ? 0 : (NT == 2) ? 1 : 2;
+    // Waves across n-tiles.  Three and four n-tiles go two to a wave: with one
+    // each, every wave converts all rows (and the fourth has no tile of
+    // three): 19 beams of 72 inputs with gains, 311 x 4992: 114 -> 105 us.
+    const int wn_shift = (NT == 1) ? 0 : (NT <= 4) ? 1 : 2;
     const int WN = 1 << wn_shift;
     const int npw = (NT + WN - 1) / WN;
     // Rows per tile: at most 64 bytes of input per thread (the prefetch
@@ -652,9 +660,18 @@ static lp_status launch_bf(const BfPlan *p, const void *x, long x_nt,
     const int tpw = tiles >= 8 ? (NT == 1 ? 2 : 4) : 1;
     dim3 grid((unsigned)((tiles + tpw - 1) / tpw), n_sb);
     // k-steps per kernel instance (KSM >= KS; the extra ones multiply
-    // zeros): the LDS rows hold KSM*16 samples.
-    const int ksm = vb == 16 ? (KS <= 6 ? 6 : KS <= 8 ? 8 : KS <= 12 ? 12 : 16)
-                             : (KS <= 8 ? 8 : 16);
+    // zeros): the LDS rows hold KSM*16 samples.  Few inputs get their own
+    // instances: padded to 6 k-steps, they spent their time zeroing the
+    // padding (8 int16 inputs, 32 x 4096: 11.8 -> 6.8 us; 16 int8 inputs, 244
+    // x 8192: 57 -> 18 us), and 9 k-steps padded to 12 took 138 instead of
+    // 114 us at the shape above.
+    auto up = [&](std::initializer_list<int> have) {
+      for (int k : have)
+        if (KS <= k) return k;
+      return 16;
+    };
+    const int ksm = vb == 16 ? up({1, 2, 3, 4, 6, 8, 9, 10, 12, 14, 16})
+                             : up({2, 4, 8, 16});
     size_t shm = (size_t)T * bf_row_stride(ksm, (int)sizeof(IT)) + ksm * 32;
     auto args = [&](auto kern) {
       LP_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
@@ -668,35 +685,32 @@ static lp_status launch_bf(const BfPlan *p, const void *x, long x_nt,
                          1.0f / (float)(row_bytes / vb));
       return LP_OK;
     };
-    // Register arrays sized to the shape: NV load vectors per thread, KSM
-    // weight fragments per n-tile.
-    const int nv = (int)(((long)T * row_bytes / vb + kBfThreads - 1) /
-                         kBfThreads);
-    lp_status rc;
-    if (vb == 16) {
-      auto by_k = [&](auto npw_c, auto nv_c) {
-        constexpr int P_ = decltype(npw_c)::value, V_ = decltype(nv_c)::value;
-        return KS <= 6    ? args(bf_mfma_kernel<IT, 16, P_, 6, V_>)
-               : KS <= 8  ? args(bf_mfma_kernel<IT, 16, P_, 8, V_>)
-               : KS <= 12 ? args(bf_mfma_kernel<IT, 16, P_, 12, V_>)
-                          : args(bf_mfma_kernel<IT, 16, P_, 16, V_>);
-      };
-      using C1 = std::integral_constant<int, 1>;
-      using C2 = std::integral_constant<int, 2>;
-      using C3 = std::integral_constant<int, 3>;
-      using C4 = std::integral_constant<int, 4>;
-      rc = npw == 1 ? (nv <= 3 ? by_k(C1(), C3()) : by_k(C1(), C4()))
-                    : (nv <= 3 ? by_k(C2(), C3()) : by_k(C2(), C4()));
-    } else {
-      const bool small_k = KS <= 8;
-#define LP_BF_PICK(VB_)                                                      \
-    (npw == 1 ? (small_k ? args(bf_mfma_kernel<IT, VB_, 1, 8, 64 / VB_>)     \
-                         : args(bf_mfma_kernel<IT, VB_, 1, 16, 64 / VB_>))   \
-              : (small_k ? args(bf_mfma_kernel<IT, VB_, 2, 8, 64 / VB_>)     \
-                         : args(bf_mfma_kernel<IT, VB_, 2, 16, 64 / VB_>)))
-      rc = (vb == 8) ? LP_BF_PICK(8) : LP_BF_PICK(4);
-#undef LP_BF_PICK
-    }
+    // Register arrays sized to the shape: KSM weight fragments per n-tile and
+    // the load vectors per thread that rows of KSM k-steps can need.
+    lp_status rc = LP_EINVAL;
+    auto run = [&](auto vb_c, auto k_c) {
+      constexpr int V = decltype(vb_c)::value, K = decltype(k_c)::value;
+      constexpr int row = K * 16 * (int)sizeof(IT);  // longest row in bytes
+      constexpr int rows = row > 128 ? 64 : 128;
+      constexpr int NV = V == 16 ? (rows * row / 16 + kBfThreads - 1) / kBfThreads
+                                 : 64 / V;
+      if constexpr (row <= 256)  // (longer rows are refused)
+        rc = npw == 1 ? args(bf_mfma_kernel<IT, V, 1, K, NV>)
+                      : args(bf_mfma_kernel<IT, V, 2, K, NV>);
+    };
+    auto pick = [&](auto vb_c, auto... k_c) {
+      // (one of them equals ksm)
+      ((decltype(k_c)::value == ksm ? run(vb_c, k_c) : void()), ...);
+    };
+#define LP_K(n) std::integral_constant<int, n>()
+    if (vb == 16)
+      pick(LP_K(16), LP_K(1), LP_K(2), LP_K(3), LP_K(4), LP_K(6), LP_K(8),
+           LP_K(9), LP_K(10), LP_K(12), LP_K(14), LP_K(16));
+    else if (vb == 8)
+      pick(LP_K(8), LP_K(2), LP_K(4), LP_K(8), LP_K(16));
+    else
+      pick(LP_K(4), LP_K(2), LP_K(4), LP_K(8), LP_K(16));
+#undef LP_K
     if (rc) return rc;
   } else {
     // k-groups of four samples per lane quarter (the kernel instance's; more
