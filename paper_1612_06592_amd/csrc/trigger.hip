@@ -8,17 +8,21 @@
 //   trials are chained while consecutive samples are at most M apart, each
 //   chain keeping its highest SNR (lowest trial, then earliest on ties).
 //
-// Four kernels, every list exact (a series of n_t windows has at most n_t/2
+// Three steps, every list exact (a series of n_t windows has at most n_t/2
 // runs, and the workspace holds that many):
-//   trig_series_kernel  one workgroup per series: sigma, fired-window
-//                       bitmask in LDS, every run's maximum in time order;
-//   trig_merge_kernel   one workgroup per beam: the rank of each trigger in
-//                       the beam's (sample, trial) order by binary searches
-//                       in the other trials' sorted lists, then the chains
-//                       by a segmented scan over the sorted sequence;
-//   trig_scan_kernel    one workgroup: each beam's first output slot, the
-//                       true total, per-series SNR / sigma, best trial;
-//   trig_copy_kernel    one workgroup per beam: its chains into the list.
+//   series  one workgroup per series: sigma, fired-window bitmask in LDS,
+//           every run's maximum in time order;
+//   merge   one workgroup per beam: the rank of each trigger in the beam's
+//           (sample, trial) order by binary searches in the other trials'
+//           sorted lists, then the chains by a segmented scan over the sorted
+//           sequence;
+//   output  one workgroup per beam: its first output slot (the earlier beams'
+//           chains), its chains into the list, SNR / sigma of its trials, its
+//           best trial, and the true total.
+// What bounds the small workloads is launches and latency, so steps that need
+// only one workgroup's results run in one kernel: series and merge with one
+// trial, merge and output with one beam, all three with both (one beam of 4096
+// windows: 18.5 us in four kernels -> 9.7 us in one; of 65536: 43 -> 25 us).
 // All reductions have a fixed order, so the result is bitwise reproducible.
 #include <cmath>
 
@@ -105,28 +109,49 @@ __device__ __forceinline__ int wg_exscan(int v, int *scratch, int *total) {
   return wave_off + incl - v;
 }
 
-// One workgroup per series.  Pass A: coalesced reads of the window maxima;
+// Series step.  Pass A: coalesced reads of the window maxima;
 // each wave's ballot gives the fired bits of 64 consecutive windows (LDS
 // bitmask).  Pass B: each thread scans a contiguous range of the bitmask
 // for run starts (a fired window whose predecessor did not fire); a
 // fixed-order scan of the counts gives each run its slot in the series'
 // list, so the list is in time order.
-__global__ __launch_bounds__(kT1Threads) void trig_series_kernel(
+__device__ __forceinline__ void series_step(
     const SynCand *__restrict__ cand, const float *__restrict__ psum,
-    long n_t, long frame0, long warm, float k_sigma, WorkLayout w) {
-  extern __shared__ unsigned bits[];          // n_t / 32 words
+    long n_t, long frame0, long warm, float k_sigma, WorkLayout w, int q,
+    unsigned *bits) {  // bits: n_t / 32 words of LDS
   __shared__ double sred[kT1Threads / 64];
   __shared__ float fred[kT1Threads / 64];
   __shared__ int ired[kT1Threads / 64];
-  const int q = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const SynCand *cq = cand + (long)q * n_t;
   const float *pq = psum + (long)q * (n_t / 16);
 
+  // The first pass-A batch of window maxima (below), in flight while sigma is
+  // formed.
+  constexpr int kU = 16;
+  float ev[kU];
+  auto batch = [&](long base0) {
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      const long m = base0 + (long)u * kT1Threads + lane;
+      ev[u] = m < n_t ? cq[m].emax : 0.0f;
+    }
+  };
+  batch((long)wave * 64);
+
   // sigma: fixed-order FP64 sum of the per-16-frame partial sums.
   const long n_part = n_t / 16;
   double acc = 0.0;
-  for (long i = tid; i < n_part; i += kT1Threads) acc += (double)pq[i];
+  for (long i = tid; i < n_part; i += 4 * kT1Threads) {
+    float v[4];  // in flight together; added in order
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const long k = i + (long)u * kT1Threads;
+      v[u] = k < n_part ? pq[k] : 0.0f;
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) acc += (double)v[u];
+  }
   for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off);
   if (lane == 0) sred[wave] = acc;
   __syncthreads();
@@ -139,28 +164,21 @@ __global__ __launch_bounds__(kT1Threads) void trig_series_kernel(
   const float thr = k_sigma * sigma;
   const float inv_sigma = sigma > 0.0f ? 1.0f / sigma : 0.0f;
 
-  // Pass A (four 64-window groups per wave and step: their loads are in
-  // flight together).
-  constexpr int kU = 4;
-  float pk = 0.0f;
+  // Pass A (sixteen 64-window groups per wave and step: their loads are in
+  // flight together; with four, one series of 65536 windows took 24 us).
+  float pk = 0.0f;  // largest maximum: over sigma below (division is monotonic)
   for (long base0 = (long)wave * 64; base0 < n_t;
        base0 += (long)kT1Threads * kU) {
-    float ev[kU];
-#pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      const long m = base0 + (long)u * kT1Threads + lane;
-      ev[u] = m < n_t ? cq[m].emax : 0.0f;
-    }
+    if (base0 >= (long)kT1Threads * kU) batch(base0);
 #pragma unroll
     for (int u = 0; u < kU; ++u) {
       const long base = base0 + (long)u * kT1Threads;
-      if (base >= n_t) break;
       const long m = base + lane;
       const float e = ev[u];
       bool valid = m < n_t && m >= first_valid && sigma > 0.0f;
-      if (valid) pk = fmaxf(pk, e / sigma);
+      if (valid) pk = fmaxf(pk, e);
       unsigned long long b = __ballot(valid && e > thr);
-      if (lane == 0) {
+      if (lane == 0 && base < n_t) {
         bits[base / 32] = (unsigned)b;
         if (base / 32 + 1 < (n_t + 31) / 32)
           bits[base / 32 + 1] = (unsigned)(b >> 32);
@@ -210,7 +228,8 @@ __global__ __launch_bounds__(kT1Threads) void trig_series_kernel(
   if (tid == 0) {
     float p = 0.0f;
     for (int i = 0; i < kT1Threads / 64; ++i) p = fmaxf(p, fred[i]);
-    w.ser_peak[q] = p;
+    // (inf / inf counts as no peak)
+    w.ser_peak[q] = sigma > 0.0f ? fmaxf(0.0f, p / sigma) : 0.0f;
     w.ser_sigma[q] = sigma;
     w.ser_inv[q] = inv_sigma;
     w.ser_cnt[q] = total;
@@ -265,7 +284,7 @@ __device__ __forceinline__ int search(const SerEnt *__restrict__ L, int n,
   return lo;
 }
 
-// One workgroup per beam.  Phase 1: every trigger of every trial of the
+// Merge step.  Phase 1: every trigger of every trial of the
 // beam gets its rank in (sample, trial) order -- its index in its own
 // trial's time-ordered list plus, for every other trial, the number of
 // entries before it (binary search) -- and is written to that rank.
@@ -276,13 +295,13 @@ __device__ __forceinline__ int search(const SerEnt *__restrict__ L, int n,
 // sum of starts for the chain ids, and a segmented maximum that carries
 // the best of the open chain from range to range -- and each chain's best
 // is written once, by the thread in whose range the chain ends.
-__global__ __launch_bounds__(kT2Threads) void trig_merge_kernel(int n_tec,
-                                                                WorkLayout w) {
-  extern __shared__ int off[];  // [n_tec + 1] first merged slot per trial
+__device__ __forceinline__ void merge_step(int n_tec, WorkLayout w, int b,
+                                           int *off) {
+  // off: LDS, [n_tec + 1] first merged slot per trial
   __shared__ int iscr[kT2Threads / 64];
   __shared__ Best bscr[kT2Threads / 64];
   __shared__ int fscr[kT2Threads / 64];
-  const int b = blockIdx.x;
+  __shared__ Best small[64];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const long s0 = (long)b * n_tec;
   const int *cnt = w.ser_cnt + s0;
@@ -291,8 +310,9 @@ __global__ __launch_bounds__(kT2Threads) void trig_merge_kernel(int n_tec,
   unsigned *chn = w.chains + s0 * w.cap_s;
 
   // Offsets of the trials' lists in the merged sequence.
-  int carry = 0;
-  for (int j0 = 0; j0 < n_tec; j0 += kT2Threads) {
+  int carry = n_tec == 1 ? cnt[0] : 0;
+  if (n_tec == 1 && tid == 0) off[0] = 0;
+  for (int j0 = 0; n_tec > 1 && j0 < n_tec; j0 += kT2Threads) {
     const int j = j0 + tid;
     const int c = j < n_tec ? cnt[j] : 0;
     int tot = 0;
@@ -303,6 +323,63 @@ __global__ __launch_bounds__(kT2Threads) void trig_merge_kernel(int n_tec,
   if (tid == 0) off[n_tec] = carry;
   __syncthreads();
   const int N = carry;
+
+  if (N <= 64) {
+    // A beam's noise triggers a few times per block: one wave merges up to 64
+    // triggers in registers, without the barriers and the round trips through
+    // memory of the general path (one beam, 4096 windows, the whole trigger:
+    // 16.7 -> 9.7 us).
+    if (wave == 0) {
+      const bool on = lane < N;
+      int lo = 0, hi = n_tec;  // largest j with off[j] <= lane
+      while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (off[mid] <= lane)
+          lo = mid;
+        else
+          hi = mid;
+      }
+      Best v = {0.0f, 0, 0, 0xffffffffu};
+      if (on) {
+        const int i = lane - off[lo];
+        const SerEnt e = lists[(long)lo * w.cap_s + i];
+        v.snr = e.peak * w.ser_inv[s0 + lo];
+        v.tec = lo;
+        v.pos = e.pos;
+        v.u = ((unsigned)lo << kIdxBits) | (unsigned)i;
+      }
+      // Rank in (sample, trial) order; within a trial samples ascend.
+      int rank = 0;
+      for (int x = 0; x < N; ++x) {
+        const int px = __shfl(v.pos, x), jx = __shfl(v.tec, x);
+        rank += px < v.pos || (px == v.pos && jx < v.tec);
+      }
+      if (on) small[rank] = v;
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      if (on) v = small[lane];
+      const int pp = __shfl_up(v.pos, 1);
+      const bool start = on && (lane == 0 || v.pos - pp > kM);
+      const unsigned long long starts = __ballot(start);
+      const int cid =
+          __popcll(starts & (~0ull >> (63 - lane))) - 1;  // chain of the lane
+      // Segmented inclusive maximum over each chain.
+      int f = start;
+      for (int o = 1; o < N; o <<= 1) {
+        const Best pv = shfl_up_best(v, o);
+        const int pf = __shfl_up(f, o);
+        if (lane >= o && !f) {
+          v = best_of(pv, v);
+          f |= pf;
+        }
+      }
+      const bool next_starts = lane < 63 && ((starts >> (lane + 1)) & 1);
+      if (on && (lane == N - 1 || next_starts)) chn[cid] = v.u;
+      if (lane == 0) w.beam_cnt[b] = __popcll(starts);
+    }
+    return;
+  }
 
   // Phase 1: ranks.
   for (int e = tid; e < N; e += kT2Threads) {
@@ -416,12 +493,135 @@ __global__ __launch_bounds__(kT2Threads) void trig_merge_kernel(int n_tec,
   if (tid == 0) w.beam_cnt[b] = n_chains;
 }
 
-// One workgroup: each beam's first slot, the true total, per-series SNR and
-// sigma, best trial per beam (lowest on ties).
-__global__ __launch_bounds__(kT2Threads) void trig_scan_kernel(
-    int n_beams, int n_tec, WorkLayout w, int *__restrict__ n_out,
+// Output step: the beam's chains, in sample order, into out[base ..] (slots
+// at or past cap are dropped; n_out keeps the true count), base the number of
+// the earlier beams' chains; SNR and sigma of its trials, its best trial
+// (lowest on ties).
+constexpr int kScanBeams = 1024;  // more beams: their counts are scanned once
+
+__device__ __forceinline__ void output_step(
+    int n_beams, int n_tec, long frame0, long offset, WorkLayout w, int b,
+    lp_trig *__restrict__ out, int cap, int *__restrict__ n_out,
     float *__restrict__ snr_out, int *__restrict__ best_tec,
     float *__restrict__ sigma_out) {
+  __shared__ int osum[kT2Threads / 64], obase[kT2Threads / 64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const long s0 = (long)b * n_tec;
+  // Chains of the earlier beams and of all beams (counts are whole numbers:
+  // any order gives the same sum).
+  int before = 0, all = 0;
+  int base = 0, total = 0;
+  if (n_beams == 1) {
+    total = w.beam_cnt[0];
+  } else if (n_beams <= kScanBeams) {
+    if (tid < n_beams) {
+      all = w.beam_cnt[tid];
+      if (tid < b) before = all;
+    }
+    for (int o = 32; o >= 1; o >>= 1) {
+      before += __shfl_xor(before, o);
+      all += __shfl_xor(all, o);
+    }
+    if (lane == 0) {
+      obase[wave] = before;
+      osum[wave] = all;
+    }
+    __syncthreads();
+    for (int i = 0; i < kT2Threads / 64; ++i) {
+      base += obase[i];
+      total += osum[i];
+    }
+  }
+  if (n_beams > kScanBeams)
+    base = w.beam_base[b];
+  else if (tid == 0 && b == 0)
+    *n_out = total;
+  for (int j = tid; j < n_tec; j += kT2Threads) {
+    if (snr_out) snr_out[s0 + j] = w.ser_peak[s0 + j];
+    if (sigma_out) sigma_out[s0 + j] = w.ser_sigma[s0 + j];
+  }
+  if (best_tec && wave == 0) {
+    // (peaks are never NaN: each is a maximum taken from 0)
+    int bj = n_tec;
+    float bp = -1.0f;
+    for (int j = lane; j < n_tec; j += 64) {
+      const float v = w.ser_peak[s0 + j];
+      if (v > bp) {
+        bp = v;
+        bj = j;
+      }
+    }
+    for (int o = 32; o >= 1; o >>= 1) {
+      const float ov = __shfl_xor(bp, o);
+      const int oj = __shfl_xor(bj, o);
+      if (ov > bp || (ov == bp && oj < bj)) {
+        bp = ov;
+        bj = oj;
+      }
+    }
+    if (lane == 0) best_tec[b] = bj;
+  }
+  const int n = w.beam_cnt[b];
+  const unsigned *chn = w.chains + s0 * w.cap_s;
+  const SerEnt *lists = w.ser_list + s0 * w.cap_s;
+  for (int c = tid; c < n && base + c < cap; c += kT2Threads) {
+    const unsigned u = chn[c];
+    const int j = (int)(u >> kIdxBits), i = (int)(u & ((1u << kIdxBits) - 1));
+    const SerEnt e = lists[(long)j * w.cap_s + i];
+    lp_trig t;
+    t.sample = frame0 * kM - offset + e.pos;
+    t.beam = b;
+    t.tec = j;
+    t.snr = e.peak * w.ser_inv[s0 + j];
+    t.peak = e.peak;
+    out[base + c] = t;
+  }
+}
+
+struct TrigArgs {
+  const SynCand *cand;
+  const float *psum;
+  long n_t, frame0, warm, offset;
+  float k_sigma;
+  int n_beams, n_tec, cap;
+  WorkLayout w;
+  lp_trig *out;
+  int *n_out;
+  float *snr_out;
+  int *best_tec;
+  float *sigma_out;
+};
+
+__global__ __launch_bounds__(kT1Threads) void trig_series_kernel(TrigArgs a) {
+  extern __shared__ unsigned dyn[];
+  series_step(a.cand, a.psum, a.n_t, a.frame0, a.warm, a.k_sigma, a.w,
+              blockIdx.x, dyn);
+}
+
+// One workgroup per beam: SERIES (one trial) forms its series first, OUTPUT
+// (one beam) writes the list as well.  A step's workspace words are read back
+// by the workgroup that wrote them, after a barrier.
+template <bool SERIES, bool OUTPUT>
+__global__ __launch_bounds__(kT2Threads) void trig_beam_kernel(TrigArgs a) {
+  static_assert(kT1Threads == kT2Threads, "one workgroup runs every step");
+  extern __shared__ unsigned dyn[];
+  const int b = blockIdx.x;
+  if (SERIES) {
+    series_step(a.cand, a.psum, a.n_t, a.frame0, a.warm, a.k_sigma, a.w, b,
+                dyn);
+    __syncthreads();
+  }
+  merge_step(a.n_tec, a.w, b, reinterpret_cast<int *>(dyn));
+  if (OUTPUT) {
+    __syncthreads();
+    output_step(a.n_beams, a.n_tec, a.frame0, a.offset, a.w, b, a.out, a.cap,
+                a.n_out, a.snr_out, a.best_tec, a.sigma_out);
+  }
+}
+
+// One workgroup: each beam's first slot and the true total.
+__global__ __launch_bounds__(kT2Threads) void trig_scan_kernel(
+    int n_beams, WorkLayout w, int *__restrict__ n_out) {
   __shared__ int iscr[kT2Threads / 64];
   const int tid = threadIdx.x;
   int carry = 0;
@@ -434,48 +634,11 @@ __global__ __launch_bounds__(kT2Threads) void trig_scan_kernel(
     carry += tot;
   }
   if (tid == 0) *n_out = carry;
-  const long ns = (long)n_beams * n_tec;
-  for (long q = tid; q < ns; q += kT2Threads) {
-    if (snr_out) snr_out[q] = w.ser_peak[q];
-    if (sigma_out) sigma_out[q] = w.ser_sigma[q];
-  }
-  if (best_tec) {
-    for (int b = tid; b < n_beams; b += kT2Threads) {
-      const float *pk = w.ser_peak + (long)b * n_tec;
-      int bj = 0;
-      float bp = pk[0];
-      for (int j = 1; j < n_tec; ++j)
-        if (pk[j] > bp) {
-          bp = pk[j];
-          bj = j;
-        }
-      best_tec[b] = bj;
-    }
-  }
 }
 
-// One workgroup per beam: its chains, in sample order, into out[base ..]
-// (slots at or past cap are dropped; n_out keeps the true count).
-__global__ __launch_bounds__(256) void trig_copy_kernel(
-    int n_tec, long frame0, long offset, WorkLayout w,
-    lp_trig *__restrict__ out, int cap) {
-  const int b = blockIdx.x;
-  const long s0 = (long)b * n_tec;
-  const int n = w.beam_cnt[b], base = w.beam_base[b];
-  const unsigned *chn = w.chains + s0 * w.cap_s;
-  const SerEnt *lists = w.ser_list + s0 * w.cap_s;
-  for (int c = threadIdx.x; c < n && base + c < cap; c += 256) {
-    const unsigned u = chn[c];
-    const int j = (int)(u >> kIdxBits), i = (int)(u & ((1u << kIdxBits) - 1));
-    const SerEnt e = lists[(long)j * w.cap_s + i];
-    lp_trig t;
-    t.sample = frame0 * kM - offset + e.pos;
-    t.beam = b;
-    t.tec = j;
-    t.snr = e.peak * w.ser_inv[s0 + j];
-    t.peak = e.peak;
-    out[base + c] = t;
-  }
+__global__ __launch_bounds__(kT2Threads) void trig_output_kernel(TrigArgs a) {
+  output_step(a.n_beams, a.n_tec, a.frame0, a.offset, a.w, blockIdx.x, a.out,
+              a.cap, a.n_out, a.snr_out, a.best_tec, a.sigma_out);
 }
 
 }  // namespace lp
@@ -601,22 +764,35 @@ lp_status trig_launch(const void *cand, int n_beams, int n_tec, long n_t,
   const SynCand *cd = reinterpret_cast<const SynCand *>(cb);
   const float *ps = reinterpret_cast<const float *>(cb + (size_t)ns * n_t * 8);
   const long offset = (long)kM * kTaps + (long)kDelay * kM;
-  const size_t shm = (size_t)((n_t + 31) / 32) * 4;
-  LP_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(trig_series_kernel),
-                             hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)shm));
-  hipLaunchKernelGGL(trig_series_kernel, dim3(ns), dim3(kT1Threads), shm, st,
-                     cd, ps, n_t, frame0, (long)(kDelay + kTaps), k_sigma, w);
-  LP_HIP(hipGetLastError());
-  hipLaunchKernelGGL(trig_merge_kernel, dim3(n_beams), dim3(kT2Threads),
-                     (size_t)(n_tec + 1) * 4, st, n_tec, w);
-  LP_HIP(hipGetLastError());
-  hipLaunchKernelGGL(trig_scan_kernel, dim3(1), dim3(kT2Threads), 0, st,
-                     n_beams, n_tec, w, n_out, snr_out, best_tec, sigma_out);
-  LP_HIP(hipGetLastError());
-  hipLaunchKernelGGL(trig_copy_kernel, dim3(n_beams), dim3(256), 0, st, n_tec,
-                     frame0, offset, w, out, cap);
-  LP_HIP(hipGetLastError());
-  return LP_OK;
+  const TrigArgs a = {cd, ps, n_t, frame0, (long)(kDelay + kTaps), offset,
+                      k_sigma, n_beams, n_tec, cap, w, out, n_out, snr_out,
+                      best_tec, sigma_out};
+  const size_t bits = (size_t)((n_t + 31) / 32) * 4;
+  const size_t offs = (size_t)(n_tec + 1) * 4;
+  auto launch = [&](auto kern, int grid, size_t shm) {
+    LP_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
+                               hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)shm));
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(kT1Threads), shm, st, a);
+    LP_HIP(hipGetLastError());
+    return LP_OK;
+  };
+  lp_status rc = LP_OK;
+  if (n_tec == 1) {
+    const size_t shm = std::max(bits, offs);
+    if (n_beams == 1) return launch(trig_beam_kernel<true, true>, 1, shm);
+    rc = launch(trig_beam_kernel<true, false>, n_beams, shm);
+  } else {
+    if ((rc = launch(trig_series_kernel, ns, bits))) return rc;
+    if (n_beams == 1) return launch(trig_beam_kernel<false, true>, 1, offs);
+    rc = launch(trig_beam_kernel<false, false>, n_beams, offs);
+  }
+  if (rc) return rc;
+  if (n_beams > kScanBeams) {
+    hipLaunchKernelGGL(trig_scan_kernel, dim3(1), dim3(kT2Threads), 0, st,
+                       n_beams, w, n_out);
+    LP_HIP(hipGetLastError());
+  }
+  return launch(trig_output_kernel, n_beams, 0);
 }
 }  // namespace lp
