@@ -172,6 +172,12 @@ __device__ __forceinline__ void wg_sum_store(float acc, float *red,
 // m' >= 15 of H, times oscale, rounded half to even and saturated to
 // [-olim, olim - 1], go to sout [series][n_sb][nf - 30] as int16 pairs).
 // xin is float, or int16 in station mode.
+// Bound by latency: one workgroup of 16 waves fills a CU's LDS, and its waves
+// wait together, at the inputs, at the barriers and in the transform.  So the
+// next eight input frames are requested before the present eight are filtered,
+// the vectors of the pending update arrive under that filtering, and the taps
+// stay in registers over all chunks (244 subbands of 32768 frames: a whole LSMR
+// iteration 345 -> 320 us with the adjoint's part, H alone 59 -> 55.5 us).
 template <int MODE>
 __global__ __launch_bounds__(kPpfThreads) void ppf_fwd_kernel(
     const void *__restrict__ xin_, const float2 *yin, float2 *yout,
@@ -234,7 +240,9 @@ __global__ __launch_bounds__(kPpfThreads) void ppf_fwd_kernel(
   const float sc = ps * (1.f / 1024.f);
 
   // Ring of the last 16 input frames of column r (slot = frame mod 16).
-  float ring[16];
+  float ring[16], g[16];  // g: taps of column r
+#pragma unroll
+  for (int t = 0; t < 16; ++t) g[t] = taps[t * kM + tid];
   ring[0] = 0.f;
 #pragma unroll
   for (int i = 1; i < 16; ++i)  // frames m0 - 15 .. m0 - 1 (zero if < 0)
@@ -244,49 +252,43 @@ __global__ __launch_bounds__(kPpfThreads) void ppf_fwd_kernel(
   for (long mc = m0; mc < m1; mc += kPpfChunk) {
     const int ro = opaque(tid);
     const int lo = opaque(tid & 63), wo = opaque(tid >> 6);
-    float g[16];
-#pragma unroll
-    for (int t = 0; t < 16; ++t) g[t] = taps[t * kM + ro];
     __syncthreads();  // the previous chunk's reads of lds are done
     // ---- FIR of column r over the chunk's 32 frames, packed in pairs.
     // Element e0 + 1024 i is frame mc + i of column r (zero for frames
     // >= F: past the view).
     const int e0 = (int)mc * kM + (kM - 1 - ro);
     float prev = 0.f;
+    float pvb[2][8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) pvb[0][i] = ldx(e0 + i * kM);
 #pragma unroll
     for (int g8 = 0; g8 < 4; ++g8) {
-      float pv[8];
+      float *const pv = pvb[g8 & 1];
+      if (g8 < 3) {
 #pragma unroll
-      for (int i = 0; i < 8; ++i) pv[i] = ldx(e0 + (8 * g8 + i) * kM);
-      if (MODE == kFwdLsmr) {
-        // Pending update (hbar_k, x_k, h_{k+1}) on the unknowns this
-        // workgroup owns, with v_{k+1} = p p_scale (frames >= F: the
-        // stores fall past the views and are dropped).
+        for (int i = 0; i < 8; ++i)
+          pvb[(g8 + 1) & 1][i] = ldx(e0 + (8 * (g8 + 1) + i) * kM);
+      }
+      // Pending update (hbar_k, x_k, h_{k+1}) on the unknowns this workgroup
+      // owns, with v_{k+1} = p p_scale (frames >= F: the stores fall past the
+      // views and are dropped).  Its vectors arrive while the group is
+      // filtered.
+      auto uoff = [&](int i) {
+        return (unsigned)(e0 + (8 * g8 + i) * kM) * 4u;
+      };
+      auto load = [](__amdgpu_buffer_rsrc_t r, unsigned o) {
+        return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, o, 0, 0));
+      };
+      auto store = [](float v, __amdgpu_buffer_rsrc_t r, unsigned o) {
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, o, 0, 0);
+      };
+      float h0[8], hb0[8], x0[8];
+      if (MODE == kFwdLsmr && !first) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-          const unsigned o = (unsigned)(e0 + (8 * g8 + i) * kM) * 4u;
-          const float v = pv[i] * ps;
-          if (first) {
-            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rh, o,
-                                                  0, 0);
-            __builtin_amdgcn_raw_buffer_store_b32(0u, rhb, o, 0, 0);
-            __builtin_amdgcn_raw_buffer_store_b32(0u, rxv, o, 0, 0);
-          } else {
-            const float h0 = __uint_as_float(
-                __builtin_amdgcn_raw_buffer_load_b32(rh, o, 0, 0));
-            const float hb =
-                h0 - c_hbar * __uint_as_float(
-                                  __builtin_amdgcn_raw_buffer_load_b32(rhb, o, 0, 0));
-            const float xn =
-                __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rxv, o, 0, 0)) +
-                c_x * hb;
-            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(hb), rhb, o,
-                                                  0, 0);
-            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(xn), rxv, o,
-                                                  0, 0);
-            __builtin_amdgcn_raw_buffer_store_b32(
-                __float_as_uint(v - c_h * h0), rh, o, 0, 0);
-          }
+          h0[i] = load(rh, uoff(i));
+          hb0[i] = load(rhb, uoff(i));
+          x0[i] = load(rxv, uoff(i));
         }
       }
 #pragma unroll
@@ -300,6 +302,22 @@ __global__ __launch_bounds__(kPpfThreads) void ppf_fwd_kernel(
           lds[(fi >> 1) * kPpfFs + pad16(ro)] = make_float2(prev, a);
         else
           prev = a;
+      }
+      if (MODE == kFwdLsmr) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const float v = pv[i] * ps;
+          if (first) {
+            store(v, rh, uoff(i));
+            store(0.f, rhb, uoff(i));
+            store(0.f, rxv, uoff(i));
+          } else {
+            const float hb = h0[i] - c_hbar * hb0[i];
+            store(hb, rhb, uoff(i));
+            store(x0[i] + c_x * hb, rxv, uoff(i));
+            store(v - c_h * h0[i], rh, uoff(i));
+          }
+        }
       }
     }
     __syncthreads();
@@ -366,6 +384,8 @@ __global__ __launch_bounds__(kPpfThreads) void ppf_fwd_kernel(
 
 // H^T (kAdjPlain: xout = H^T y) or one LSMR half-step (kAdjLsmr: p =
 // H^T (q u_scale) - v_scale p in place, with norm partials).
+// 244 subbands of 32768 frames: 73.5 us with a branch per filtered frame, 64 us
+// with eight unconditional chains.
 template <int MODE>
 __global__ __launch_bounds__(kPpfThreads) void ppf_adj_kernel(
     const float2 *__restrict__ yin, float *pio,
@@ -408,9 +428,12 @@ __global__ __launch_bounds__(kPpfThreads) void ppf_adj_kernel(
     is *= st[series].u_scale;
     vs = st[series].v_scale;
   }
-  float ring[16];
+  float ring[16], g[16];  // g: taps of column r
 #pragma unroll
-  for (int i = 0; i < 16; ++i) ring[i] = 0.f;
+  for (int i = 0; i < 16; ++i) {
+    ring[i] = 0.f;
+    g[i] = taps[i * kM + tid];
+  }
   float acc = 0.f;
   const int n_chunk = (int)((wend - j0 + kPpfChunk - 1) / kPpfChunk);
   for (int c = 0; c < n_chunk; ++c) {
@@ -449,41 +472,53 @@ __global__ __launch_bounds__(kPpfThreads) void ppf_adj_kernel(
       fft1024_wave<false, false>(lds + wo * kPpfFs, tw_p1, tw_p2, lo);
       __syncthreads();
     }
-    // ---- Anti-causal FIR: frame jj = m - 15 once W_m has arrived.
-    float g[16];
-#pragma unroll
-    for (int t = 0; t < 16; ++t) g[t] = taps[t * kM + ro];
+    // ---- Anti-causal FIR: frame jj = m - 15 once W_m has arrived.  Eight
+    // frames at a time, every one computed (their sums are independent chains;
+    // a branch per frame would leave one chain to run alone) and those that
+    // this workgroup does not own stored past the view's end, where a store is
+    // dropped and a load reads zero.
+    float2 *const col = lds + pad16(ro);
 #pragma unroll
     for (int g8 = 0; g8 < 4; ++g8) {
-      float pold[8];
+      float cur[8], pold[8], a[8];
+      unsigned off[8];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const long jj = mc + 8 * g8 + i - (kTaps - 1);
-        pold[i] = 0.f;
-        if (MODE == kAdjLsmr && vs != 0.f && jj >= j0 && jj < jend)
-          pold[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
-              rp, (unsigned)((int)jj * kM + (kM - 1 - ro)) * 4u, 0, 0));
+      for (int i = 0; i < 4; ++i) {
+        const float2 w2 = col[(4 * g8 + i) * kPpfFs];
+        cur[2 * i] = w2.x;
+        cur[2 * i + 1] = w2.y;
       }
-      float2 w2 = make_float2(0.f, 0.f);
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        const int fi = 8 * g8 + i;
-        if (!(fi & 1)) w2 = lds[(fi >> 1) * kPpfFs + pad16(ro)];
-        ring[fi & 15] = (fi & 1) ? w2.y : w2.x;
-        const long jj = mc + fi - (kTaps - 1);
-        if (jj >= j0 && jj < jend) {
-          float a = 0.f;
+        const int jj = (int)mc + 8 * g8 + i - (kTaps - 1);
+        off[i] = jj >= (int)j0 && jj < (int)jend
+                     ? (unsigned)(jj * kM + (kM - 1 - ro)) * 4u
+                     : 0xfffffff0u;
+        // (with v_scale 0 there is no old p: it may hold anything)
+        pold[i] = MODE != kAdjLsmr ? 0.f
+                                   : __uint_as_float(
+                                         __builtin_amdgcn_raw_buffer_load_b32(
+                                             rp, vs != 0.f ? off[i] : 0xfffffff0u,
+                                             0, 0));
+        a[i] = 0.f;
+      }
 #pragma unroll
-          for (int t = 0; t < 16; ++t)
-            a = fmaf(g[t], ring[(fi - 15 + t) & 15], a);
-          if (MODE == kAdjLsmr) {
-            a = fmaf(-vs, pold[i], a);
-            acc = fmaf(a, a, acc);
-          }
-          __builtin_amdgcn_raw_buffer_store_b32(
-              __float_as_uint(a), rp,
-              (unsigned)((int)jj * kM + (kM - 1 - ro)) * 4u, 0, 0);
+      for (int t = 0; t < 16; ++t)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          // frame 8 g8 + i - 15 + t of the chunk
+          const int k = i - 15 + t;
+          a[i] = fmaf(g[t], k >= 0 ? cur[k] : ring[(8 * g8 + k) & 15], a[i]);
         }
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        ring[(8 * g8 + i) & 15] = cur[i];
+        if (MODE == kAdjLsmr) {
+          a[i] = fmaf(-vs, pold[i], a[i]);
+          if (off[i] != 0xfffffff0u) acc = fmaf(a[i], a[i], acc);
+        }
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(a[i]), rp, off[i],
+                                              0, 0);
       }
     }
   }
