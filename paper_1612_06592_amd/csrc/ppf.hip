@@ -57,7 +57,7 @@ struct LsmrState {
   float u_scale;  // u = q * u_scale              (1 / beta_{k+1})
   float v_scale;  // p_new = H^T u - v_scale * p  (beta_{k+1} / alpha_k)
   float c_hbar, c_x, c_h;  // pending elementwise update
-  int first;      // no update yet: h = v, hbar = x = 0
+  float c_x_prev;          // c_x of the update before it
   int done;       // the bidiagonalisation ended (alpha or beta zero)
 };
 static_assert(sizeof(LsmrState) <= kPpfStateBytes, "state size");
@@ -177,7 +177,9 @@ __device__ __forceinline__ void wg_sum_store(float acc, float *red,
 // next eight input frames are requested before the present eight are filtered,
 // the vectors of the pending update arrive under that filtering, and the taps
 // stay in registers over all chunks (244 subbands of 32768 frames: a whole LSMR
-// iteration 345 -> 320 us with the adjoint's part, H alone 59 -> 55.5 us).
+// iteration 345 -> 320 us with the adjoint's part, H alone 59 -> 55.5 us).  An
+// iteration is bound by HBM beyond that: p, h, hbar and x are 134 MB each there,
+// and leaving x alone in every second iteration took it from 320 to 287 us.
 template <int MODE>
 __global__ __launch_bounds__(kPpfThreads) void ppf_fwd_kernel(
     const void *__restrict__ xin_, const float2 *yin, float2 *yout,
@@ -185,7 +187,8 @@ __global__ __launch_bounds__(kPpfThreads) void ppf_fwd_kernel(
     const LsmrState *__restrict__ st, float *__restrict__ part,
     const short *__restrict__ kbin, const float *__restrict__ taps,
     const float2 *__restrict__ tw, int n_sb, long nf, int per_wg, int n_part,
-    float oscale = 1.f, int olim = 0, short2 *__restrict__ sout = nullptr) {
+    int iter = 0, float oscale = 1.f, int olim = 0,
+    short2 *__restrict__ sout = nullptr) {
   __shared__ float2 lds[16 * kPpfFs];
   __shared__ float2 tw_p1[kTwP1], tw_p2[kTwP2];
   __shared__ float red[16];
@@ -226,8 +229,7 @@ __global__ __launch_bounds__(kPpfThreads) void ppf_fwd_kernel(
       yout + (long)series * n_sb * nf, 0, ybytes, kRawBufferWord3);
   fill_tw_tables(tw, tw_p1, tw_p2);  // used after the first FIR barrier
   // Taps are g = 1024 h: fold 1 / 1024 into the input scale (exact).
-  float ps = 1.f, qs = 0.f, c_hbar = 0.f, c_x = 0.f, c_h = 0.f;
-  int first = 0;
+  float ps = 1.f, qs = 0.f, c_hbar = 0.f, c_x = 0.f, c_h = 0.f, c_xp = 0.f;
   if (MODE == kFwdLsmr) {
     const LsmrState &S = st[series];
     ps = S.p_scale;
@@ -235,7 +237,7 @@ __global__ __launch_bounds__(kPpfThreads) void ppf_fwd_kernel(
     c_hbar = S.c_hbar;
     c_x = S.c_x;
     c_h = S.c_h;
-    first = S.first;
+    c_xp = S.c_x_prev;
   }
   const float sc = ps * (1.f / 1024.f);
 
@@ -269,10 +271,12 @@ __global__ __launch_bounds__(kPpfThreads) void ppf_fwd_kernel(
         for (int i = 0; i < 8; ++i)
           pvb[(g8 + 1) & 1][i] = ldx(e0 + (8 * (g8 + 1) + i) * kM);
       }
-      // Pending update (hbar_k, x_k, h_{k+1}) on the unknowns this workgroup
-      // owns, with v_{k+1} = p p_scale (frames >= F: the stores fall past the
-      // views and are dropped).  Its vectors arrive while the group is
-      // filtered.
+      // Pending update (hbar_k, x_k, h_{k+1}, k = iter - 1) on the unknowns
+      // this workgroup owns, with v_{k+1} = p p_scale (frames >= F: the stores
+      // fall past the views and are dropped).  Its vectors arrive while the
+      // group is filtered.  x is brought up to date only after every second
+      // iteration (k even), by both additions in their order: hbar_{k-1} is
+      // at hand then as hbar's old value.  hbar_0 = x_0 = 0 are never stored.
       auto uoff = [&](int i) {
         return (unsigned)(e0 + (8 * g8 + i) * kM) * 4u;
       };
@@ -283,12 +287,13 @@ __global__ __launch_bounds__(kPpfThreads) void ppf_fwd_kernel(
         __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, o, 0, 0);
       };
       float h0[8], hb0[8], x0[8];
-      if (MODE == kFwdLsmr && !first) {
+      const bool upx = (iter & 1) != 0;
+      if (MODE == kFwdLsmr && iter > 1) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
           h0[i] = load(rh, uoff(i));
-          hb0[i] = load(rhb, uoff(i));
-          x0[i] = load(rxv, uoff(i));
+          hb0[i] = iter > 2 ? load(rhb, uoff(i)) : 0.f;
+          x0[i] = upx && iter > 3 ? load(rxv, uoff(i)) : 0.f;
         }
       }
 #pragma unroll
@@ -307,14 +312,13 @@ __global__ __launch_bounds__(kPpfThreads) void ppf_fwd_kernel(
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
           const float v = pv[i] * ps;
-          if (first) {
+          if (iter == 1) {
             store(v, rh, uoff(i));
-            store(0.f, rhb, uoff(i));
-            store(0.f, rxv, uoff(i));
           } else {
             const float hb = h0[i] - c_hbar * hb0[i];
             store(hb, rhb, uoff(i));
-            store(x0[i] + c_x * hb, rxv, uoff(i));
+            if (upx)
+              store(fmaf(c_x, hb, fmaf(c_xp, hb0[i], x0[i])), rxv, uoff(i));
             store(v - c_h * h0[i], rh, uoff(i));
           }
         }
@@ -571,7 +575,6 @@ __global__ void lsmr_init_beta_kernel(const float *__restrict__ part,
   LsmrState S = {};
   S.beta = sqrt(b2);
   S.u_scale = safe_div(1.0, S.beta);
-  S.first = 1;
   S.done = (S.beta == 0.0);
   st[series] = S;
 }
@@ -594,8 +597,7 @@ __global__ void lsmr_init_alpha_kernel(const float *__restrict__ part,
   S.p_scale = safe_div(1.0, S.alpha);
   S.q_scale = safe_div(S.alpha, S.beta);
   S.u_scale = S.v_scale = 0.f;
-  S.c_hbar = S.c_x = S.c_h = 0.f;
-  S.first = 1;
+  S.c_hbar = S.c_x = S.c_h = S.c_x_prev = 0.f;
   st[series] = S;
   if (anorm) anorm[(long)series * anorm_stride] = fabs(S.zetabar);
 }
@@ -628,9 +630,9 @@ __global__ void lsmr_alpha_kernel(const float *__restrict__ part, int n_part,
   double *an = anorm ? anorm + (long)series * anorm_stride : nullptr;
   if (S.done) {
     S.p_scale = S.q_scale = 0.f;
+    S.c_x_prev = S.c_x;
     S.c_hbar = S.c_x = S.c_h = 0.f;
-    S.first = 0;
-    st[series] = S;
+      st[series] = S;
     if (an) an[k] = an[k - 1];
     return;
   }
@@ -653,6 +655,7 @@ __global__ void lsmr_alpha_kernel(const float *__restrict__ part, int n_part,
   // hbar_k = h_k - c_hbar hbar_{k-1}; x_k = x_{k-1} + c_x hbar_k;
   // h_{k+1} = v_{k+1} - c_h h_k.
   S.c_hbar = (float)(thetabar * rho / (rho_old * rhobar_old));
+  S.c_x_prev = S.c_x;
   S.c_x = (float)(zeta / (rho * rhobar));
   S.c_h = (float)(theta_new / rho);
   S.rho = rho;
@@ -660,29 +663,30 @@ __global__ void lsmr_alpha_kernel(const float *__restrict__ part, int n_part,
   S.alpha = alpha_new;
   S.p_scale = safe_div(1.0, alpha_new);
   S.q_scale = safe_div(alpha_new, S.beta);
-  S.first = 0;
   if (S.beta == 0.0 || alpha_new == 0.0) S.done = 1;
   st[series] = S;
   if (an) an[k] = fabs(S.zetabar);
 }
 
-// The last iteration's update of x (x_K = x_{K-1} + c_x (h_K - c_hbar
-// hbar_{K-1})); with no iteration done, x = 0.
+// The last iteration's update of x: x_K = x_{K-1} + c_x hbar_K, hbar_K = h_K -
+// c_hbar hbar_{K-1}; x_{K-1} = x_{K-2} + c_x_prev hbar_{K-1} is formed here too
+// where K is even.  hbar_0 = 0 and x_0 = 0 are not read (nothing wrote them);
+// with no iteration done, x = 0.  N is a multiple of 1024.
 __global__ __launch_bounds__(256) void lsmr_final_kernel(
     float *__restrict__ x, const float *__restrict__ hv,
     const float *__restrict__ hbar, const LsmrState *__restrict__ st,
-    long N) {
+    long N, int K) {
   const int series = blockIdx.y;
   const LsmrState &S = st[series];
-  const long base = (long)series * N;
-  const long i = (long)blockIdx.x * 256 + threadIdx.x;
-  if (i >= N) return;
-  if (S.first) {
-    x[base + i] = 0.f;
-  } else {
-    const float hb = hv[base + i] - S.c_hbar * hbar[base + i];
-    x[base + i] = fmaf(S.c_x, hb, x[base + i]);
+  const long o = (long)series * N + (long)blockIdx.x * 256 + threadIdx.x;
+  if (K == 0) {
+    x[o] = 0.f;
+    return;
   }
+  const float hb0 = K == 1 ? 0.f : hbar[o];
+  float v = K <= 2 ? 0.f : x[o];
+  if ((K & 1) == 0) v = fmaf(S.c_x_prev, hb0, v);
+  x[o] = fmaf(S.c_x, hv[o] - S.c_hbar * hb0, v);
 }
 
 __global__ void ppf_rnorm_kernel(const float *__restrict__ part, int n_part,
@@ -993,7 +997,7 @@ extern "C" lp_status lp_ppf_invert(lp_ctx *ctx, const lp_band *band,
     // beta_{k+1} u_{k+1} = H v_k - alpha_k u_k (u_1 is y itself).
     hipLaunchKernelGGL(ppf_fwd_kernel<kFwdLsmr>, gf, blk, 0, hs, pv,
                        k == 1 ? yv : q, q, hv, hb, x, st, part, kbin, taps,
-                       tw, S, nf, rf.per_wg, rf.n_wg);
+                       tw, S, nf, rf.per_wg, rf.n_wg, k);
     hipLaunchKernelGGL(lsmr_beta_kernel, dim3(n_series), dim3(64), 0, hs,
                        part, rf.n_wg, st);
     // alpha_{k+1} v_{k+1} = H^T u_{k+1} - beta_{k+1} v_k.
@@ -1003,8 +1007,8 @@ extern "C" lp_status lp_ppf_invert(lp_ctx *ctx, const lp_band *band,
                        part, ra.n_wg, st, anorm, an_stride, k);
   }
   hipLaunchKernelGGL(lsmr_final_kernel,
-                     dim3((unsigned)((L.N + 255) / 256), n_series), dim3(256),
-                     0, hs, x, hv, hb, st, L.N);
+                     dim3((unsigned)(L.N / 256), n_series), dim3(256),
+                     0, hs, x, hv, hb, st, L.N, n_iter);
   if (rnorm) {
     hipLaunchKernelGGL(ppf_fwd_kernel<kFwdResid>, gf, blk, 0, hs, x, yv,
                        (float2 *)nullptr, nullptr, nullptr, nullptr, st,
@@ -1060,7 +1064,7 @@ extern "C" lp_status lp_station_ppf(lp_ctx *ctx, const lp_band *band,
                      (float2 *)nullptr, nullptr, nullptr, nullptr, nullptr,
                      nullptr, p->kbin.as<const short>(),
                      p->taps.as<const float>(), ctx->tw4096.as<const float2>(),
-                     band->n_sb, nf, rf.per_wg, 0, scale, dtype == LP_CI8 ? 128 : 32768,
+                     band->n_sb, nf, rf.per_wg, 0, 0, scale, dtype == LP_CI8 ? 128 : 32768,
                      stage);
   const long P = (long)band->n_sb * n_frames;
   const bool ci8 = dtype == LP_CI8;
