@@ -30,6 +30,7 @@
 // one-wave kernels between the operator launches, on the same stream, so
 // a solve needs no host synchronisation.  Vectors are FP32 in HBM.
 #include <cmath>
+#include <type_traits>
 
 #include "fft_dev.h"
 #include "lp_internal.h"
@@ -180,7 +181,9 @@ __device__ __forceinline__ void wg_sum_store(float acc, float *red,
 // iteration 345 -> 320 us with the adjoint's part, H alone 59 -> 55.5 us).  An
 // iteration is bound by HBM beyond that: p, h, hbar and x are 134 MB each there,
 // and leaving x alone in every second iteration took it from 320 to 287 us.
-template <int MODE>
+// STREAM: how many of x, hbar and h (in this order) bypass the caches; the
+// caller's rule took it from there to 249 us.
+template <int MODE, int STREAM = 0>
 __global__ __launch_bounds__(kPpfThreads) void ppf_fwd_kernel(
     const void *__restrict__ xin_, const float2 *yin, float2 *yout,
     float *__restrict__ hv, float *__restrict__ hbar, float *__restrict__ xv,
@@ -280,20 +283,26 @@ __global__ __launch_bounds__(kPpfThreads) void ppf_fwd_kernel(
       auto uoff = [&](int i) {
         return (unsigned)(e0 + (8 * g8 + i) * kM) * 4u;
       };
-      auto load = [](__amdgpu_buffer_rsrc_t r, unsigned o) {
-        return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, o, 0, 0));
+      // (bit 1 of a buffer access's last argument: nontemporal)
+      const std::integral_constant<int, STREAM >= 1 ? 2 : 0> ntx{};
+      const std::integral_constant<int, STREAM >= 2 ? 2 : 0> nthb{};
+      const std::integral_constant<int, STREAM >= 3 ? 2 : 0> nth{};
+      auto load = [](__amdgpu_buffer_rsrc_t r, unsigned o, auto nt) {
+        return __uint_as_float(
+            __builtin_amdgcn_raw_buffer_load_b32(r, o, 0, decltype(nt)::value));
       };
-      auto store = [](float v, __amdgpu_buffer_rsrc_t r, unsigned o) {
-        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, o, 0, 0);
+      auto store = [](float v, __amdgpu_buffer_rsrc_t r, unsigned o, auto nt) {
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, o, 0,
+                                              decltype(nt)::value);
       };
       float h0[8], hb0[8], x0[8];
       const bool upx = (iter & 1) != 0;
       if (MODE == kFwdLsmr && iter > 1) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-          h0[i] = load(rh, uoff(i));
-          hb0[i] = iter > 2 ? load(rhb, uoff(i)) : 0.f;
-          x0[i] = upx && iter > 3 ? load(rxv, uoff(i)) : 0.f;
+          h0[i] = load(rh, uoff(i), nth);
+          hb0[i] = iter > 2 ? load(rhb, uoff(i), nthb) : 0.f;
+          x0[i] = upx && iter > 3 ? load(rxv, uoff(i), ntx) : 0.f;
         }
       }
 #pragma unroll
@@ -313,13 +322,13 @@ __global__ __launch_bounds__(kPpfThreads) void ppf_fwd_kernel(
         for (int i = 0; i < 8; ++i) {
           const float v = pv[i] * ps;
           if (iter == 1) {
-            store(v, rh, uoff(i));
+            store(v, rh, uoff(i), nth);
           } else {
             const float hb = h0[i] - c_hbar * hb0[i];
-            store(hb, rhb, uoff(i));
+            store(hb, rhb, uoff(i), nthb);
             if (upx)
-              store(fmaf(c_x, hb, fmaf(c_xp, hb0[i], x0[i])), rxv, uoff(i));
-            store(v - c_h * h0[i], rh, uoff(i));
+              store(fmaf(c_x, hb, fmaf(c_xp, hb0[i], x0[i])), rxv, uoff(i), ntx);
+            store(v - c_h * h0[i], rh, uoff(i), nth);
           }
         }
       }
@@ -405,10 +414,13 @@ __global__ __launch_bounds__(kPpfThreads) void ppf_adj_kernel(
   // or -1: [q][j].
   __shared__ int soff[16 * 64];
 
-  const int series = blockIdx.y;
+  // From the last run to the first: what H touched last is still cached (8
+  // series of 16384 frames: 1059 -> 1023 us an LSMR iteration).
+  const int series = gridDim.y - 1 - blockIdx.y;
+  const int run = gridDim.x - 1 - blockIdx.x;
   const long F = nf - (kTaps - 1);
   const long N = F * kM;
-  const long j0 = (long)blockIdx.x * per_wg;
+  const long j0 = (long)run * per_wg;
   const long jend = min(j0 + (long)per_wg, F);
   const long wend = jend + (kTaps - 1);  // W frames [j0, wend) are used
   const int tid = threadIdx.x;
@@ -527,7 +539,7 @@ __global__ __launch_bounds__(kPpfThreads) void ppf_adj_kernel(
     }
   }
   if (MODE == kAdjLsmr)
-    wg_sum_store(acc, red, part + (long)series * n_part + blockIdx.x);
+    wg_sum_store(acc, red, part + (long)series * n_part + run);
 }
 
 // Partial sums of |y|^2 (kPpfNormParts contiguous slices per series).
@@ -984,6 +996,20 @@ extern "C" lp_status lp_ppf_invert(lp_ctx *ctx, const lp_band *band,
                 ra = ppf_runs(ctx->n_cu, n_series, L.F, true);
   const dim3 gf(rf.n_wg, n_series), ga(ra.n_wg, n_series), blk(kPpfThreads);
 
+  // H stores u_k and p_k for the adjoint and the adjoint for H: kept in the
+  // memory-side cache (256 MB), they need not come from HBM.  Of h, hbar and x,
+  // which only H touches, as many as fit beside them take part; the others
+  // stream past it.  us per iteration with 0, 1, 2, 3 of them streaming, by
+  // the megabytes of p, u, h, hbar and x together: 150: 78, 79, 79, 83; 300:
+  // 137, 130, 132, 141; 450: 221, 217, 190, 201; 600: 293, 289, 277, 256;
+  // 1200: 549, 545, 536, 516.
+  const size_t vec = (size_t)n_series * L.N * 4,
+               both = vec + (size_t)n_series * S * nf * 8;
+  constexpr size_t cache = 256u << 20;
+  auto *fwd = both + 3 * vec <= cache   ? ppf_fwd_kernel<kFwdLsmr, 0>
+              : both + 2 * vec <= cache ? ppf_fwd_kernel<kFwdLsmr, 1>
+              : both + vec <= cache     ? ppf_fwd_kernel<kFwdLsmr, 2>
+                                        : ppf_fwd_kernel<kFwdLsmr, 3>;
   // beta_1 u_1 = y; alpha_1 v_1 = H^T u_1.
   hipLaunchKernelGGL(ppf_sumsq_kernel, dim3(kPpfNormParts, n_series),
                      dim3(256), 0, hs, yv, (long)S * nf, part);
@@ -995,9 +1021,10 @@ extern "C" lp_status lp_ppf_invert(lp_ctx *ctx, const lp_band *band,
                      part, ra.n_wg, st, anorm, an_stride);
   for (int k = 1; k <= n_iter; ++k) {
     // beta_{k+1} u_{k+1} = H v_k - alpha_k u_k (u_1 is y itself).
-    hipLaunchKernelGGL(ppf_fwd_kernel<kFwdLsmr>, gf, blk, 0, hs, pv,
+    hipLaunchKernelGGL(fwd, gf, blk, 0, hs, pv,
                        k == 1 ? yv : q, q, hv, hb, x, st, part, kbin, taps,
-                       tw, S, nf, rf.per_wg, rf.n_wg, k);
+                       tw, S, nf, rf.per_wg, rf.n_wg, k, 1.f, 0,
+                       (short2 *)nullptr);
     hipLaunchKernelGGL(lsmr_beta_kernel, dim3(n_series), dim3(64), 0, hs,
                        part, rf.n_wg, st);
     // alpha_{k+1} v_{k+1} = H^T u_{k+1} - beta_{k+1} v_k.

@@ -36,3 +36,29 @@ def test_every_iteration_count(n_iter):
                                   n_iter)
         assert np.linalg.norm(got[i] - want) <= 2e-6 * n_iter * np.linalg.norm(want)
     ctx.close()
+
+
+@pytest.mark.parametrize("ns", [9, 12, 20])
+def test_streaming_of_the_vectors_does_not_show(ns):
+    """Many equal series, so that 1, 2 or 3 of the vectors bypass the caches,
+    against one series alone (none does).  The cut into runs differs, so the
+    norms are summed in another order (1e-7 in each partial sum's FP32): 5
+    iterates agree within 1e-5."""
+    import torch
+    nf, k, n_iter = 2048, np.arange(120, 160, dtype=np.int32), 5
+    g = torch.Generator(device="cuda:0").manual_seed(ns)
+    y = torch.randn((1, len(k), nf, 2), generator=g, device="cuda:0")
+    ctx, band = lp.Ctx(0), lp.Band(k)
+
+    def solve(y, ns):
+        x = torch.full((ns, (nf - 15) * 1024), float("nan"), device="cuda:0")
+        nb = lp.nbytes("lp_ppf_work_bytes", len(k), ns, nf)
+        work = torch.full((nb // 4,), float("nan"), device="cuda:0")
+        lp.ppf_invert(ctx, band, y, ns, nf, n_iter, x, work.view(torch.uint8))
+        return x.double()
+
+    one = solve(y, 1)[0]
+    many = solve(y.expand(ns, -1, -1, -1).contiguous(), ns)
+    for i in range(ns):
+        assert torch.linalg.norm(many[i] - one) <= 1e-5 * torch.linalg.norm(one)
+    ctx.close()
