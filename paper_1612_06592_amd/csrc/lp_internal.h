@@ -284,6 +284,28 @@ lp_status trig_launch(const void *cand, int n_beams, int n_tec, long n_t,
                       int *n_out, float *snr_out, int *best_tec,
                       float *sigma_out, void *work, hipStream_t st);
 
+// The memory-side cache: what a kernel leaves there in less than this many
+// bytes, the next one need not read from HBM.  Results that exceed it are
+// better written past it.
+constexpr size_t kMallBytes = 256u << 20;
+
+// Nontemporal accesses of N floats, aligned to their size.
+template <int N>
+__device__ __forceinline__ void nt_store(void *p, const float *v) {
+  typedef float vec __attribute__((ext_vector_type(N)));
+  vec o;
+#pragma unroll
+  for (int i = 0; i < N; ++i) o[i] = v[i];
+  __builtin_nontemporal_store(o, static_cast<vec *>(p));
+}
+template <int N>
+__device__ __forceinline__ void nt_load(const void *p, float *v) {
+  typedef float vec __attribute__((ext_vector_type(N)));
+  const vec o = __builtin_nontemporal_load(static_cast<const vec *>(p));
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] = o[i];
+}
+
 // Remap a linear block index so that consecutive logical blocks land on the
 // same XCD (blocks are dealt round-robin over the 8 XCDs of the chip).
 __device__ inline long xcd_remap(long bid, long nblocks) {

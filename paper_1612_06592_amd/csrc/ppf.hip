@@ -1005,11 +1005,10 @@ extern "C" lp_status lp_ppf_invert(lp_ctx *ctx, const lp_band *band,
   // 1200: 549, 545, 536, 516.
   const size_t vec = (size_t)n_series * L.N * 4,
                both = vec + (size_t)n_series * S * nf * 8;
-  constexpr size_t cache = 256u << 20;
-  auto *fwd = both + 3 * vec <= cache   ? ppf_fwd_kernel<kFwdLsmr, 0>
-              : both + 2 * vec <= cache ? ppf_fwd_kernel<kFwdLsmr, 1>
-              : both + vec <= cache     ? ppf_fwd_kernel<kFwdLsmr, 2>
-                                        : ppf_fwd_kernel<kFwdLsmr, 3>;
+  auto *fwd = both + 3 * vec <= kMallBytes   ? ppf_fwd_kernel<kFwdLsmr, 0>
+              : both + 2 * vec <= kMallBytes ? ppf_fwd_kernel<kFwdLsmr, 1>
+              : both + vec <= kMallBytes     ? ppf_fwd_kernel<kFwdLsmr, 2>
+                                             : ppf_fwd_kernel<kFwdLsmr, 3>;
   // beta_1 u_1 = y; alpha_1 v_1 = H^T u_1.
   hipLaunchKernelGGL(ppf_sumsq_kernel, dim3(kPpfNormParts, n_series),
                      dim3(256), 0, hs, yv, (long)S * nf, part);

@@ -18,6 +18,7 @@
 // in registers and writes every final beam that uses them (coalesced in t).
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "lp_internal.h"
 
@@ -28,8 +29,10 @@ constexpr int kTsMaxGroups = 32;
 
 // NS samples per thread (1, or 2 with 16-byte accesses when n_t is even
 // and both arrays are 16-byte aligned); GMAX >= G bounds the registers
-// that hold the groups' samples.
-template <int NS, int GMAX>
+// that hold the groups' samples.  Bound by HBM.  STREAM: the beams exceed the
+// memory-side cache, so that both they and the preliminary beams pass it by (8
+// groups x 7 and 61 beams, 122 x 8192 samples: 180 -> 171 us, 5.5 TB/s).
+template <int NS, int GMAX, bool STREAM>
 __global__ __launch_bounds__(kTsThreads) void ts_stage2_kernel(
     const float2 *__restrict__ y1, const float2 *__restrict__ coef,
     const int *__restrict__ order, const int *__restrict__ pstart, int G,
@@ -49,14 +52,19 @@ __global__ __launch_bounds__(kTsThreads) void ts_stage2_kernel(
 #pragma unroll
     for (int g = 0; g < GMAX; ++g) {
       const float2 *src = y1 + ((long)(g * P + p) * n_sb + s) * n_t + t;
-      if constexpr (NS == 2) {
-        const float4 q = (g < G) ? *reinterpret_cast<const float4 *>(src)
-                                 : make_float4(0.f, 0.f, 0.f, 0.f);
-        v[g][0] = make_float2(q.x, q.y);
-        v[g][1] = make_float2(q.z, q.w);
-      } else {
-        v[g][0] = (g < G) ? *src : make_float2(0.f, 0.f);
+      float q[2 * NS] = {};
+      if (g < G) {
+        if constexpr (STREAM) {
+          nt_load<2 * NS>(src, q);
+        } else if constexpr (NS == 2) {
+          const float4 w = *reinterpret_cast<const float4 *>(src);
+          q[0] = w.x, q[1] = w.y, q[2] = w.z, q[3] = w.w;
+        } else {
+          q[0] = src->x, q[1] = src->y;
+        }
       }
+#pragma unroll
+      for (int k = 0; k < NS; ++k) v[g][k] = make_float2(q[2 * k], q[2 * k + 1]);
     }
     for (int i = b0; i < b1; ++i) {
       const int b = order[i];
@@ -76,10 +84,16 @@ __global__ __launch_bounds__(kTsThreads) void ts_stage2_kernel(
         }
       }
       float2 *dst = y + ((long)b * n_sb + s) * n_t + t;
-      if constexpr (NS == 2)
+      if constexpr (STREAM) {
+        float o[2 * NS];
+#pragma unroll
+        for (int k = 0; k < NS; ++k) o[2 * k] = ar[k], o[2 * k + 1] = ai[k];
+        nt_store<2 * NS>(dst, o);
+      } else if constexpr (NS == 2) {
         *reinterpret_cast<float4 *>(dst) = make_float4(ar[0], ai[0], ar[1], ai[1]);
-      else
+      } else {
         *dst = make_float2(ar[0], ai[0]);
+      }
     }
   }
 }
@@ -313,9 +327,15 @@ extern "C" lp_status lp_beamform_stage2(lp_ctx *ctx, const lp_array *array,
   dim3 grid((unsigned)((n_t + per_wg - 1) / per_wg), band->n_sb);
   size_t shm = (size_t)p->B * p->G * sizeof(float2);
   // (Two samples of up to 32 groups would take 145 registers.)
-  auto *kern = p->G > 8 ? ts_stage2_kernel<1, kTsMaxGroups>
-               : two    ? ts_stage2_kernel<2, 8>
-                        : ts_stage2_kernel<1, 8>;
+  auto pick = [&](auto stream) {
+    constexpr bool ST = decltype(stream)::value;
+    return p->G > 8 ? ts_stage2_kernel<1, kTsMaxGroups, ST>
+           : two    ? ts_stage2_kernel<2, 8, ST>
+                    : ts_stage2_kernel<1, 8, ST>;
+  };
+  auto *kern = (size_t)p->B * band->n_sb * n_t * sizeof(float2) > kMallBytes
+                   ? pick(std::true_type())
+                   : pick(std::false_type());
   hipLaunchKernelGGL(kern, grid, dim3(kTsThreads), shm, st,
                      static_cast<const float2 *>(y1), p->coef.as<const float2>(),
                      p->order.as<const int>(), p->pstart.as<const int>(),
