@@ -26,7 +26,11 @@
 // 4160 -> 3446 us, by taps that stay in registers (they were read again every
 // chunk, after the barrier), FIR sums in eight independent chains, a store of
 // the series that is no branch where it is not asked for, butterflies in FMA
-// form, and the next inputs requested before the barrier.  Tried and slower:
+// form, and the next inputs requested before the barrier; then by 2 to 18 %,
+more with more subbands, by spreading those requests over the filter.  Tried and
+slower: inputs read by rows and handed over through LDS (three barriers, 3640
+us), two halves of eight frames of which one is transformed while the other is
+filtered (4017 us),
 // envelope maxima in registers with the two barriers side by side (3944 to
 // 4359 us), pass 0 of the next chunk under the arg-max reads (3741), the
 // square roots of a chunk by one wave (3667).
@@ -119,6 +123,13 @@ __global__ __launch_bounds__(kSynThreads) void syn_kernel(
   // series size for an empty bin (a raw buffer load past the end reads 0).
   __shared__ unsigned roff_s[8 * 64];
 
+  // A load of the inputs touches 64 rows, one address lookup each, and all 16
+  // waves load at the same time: issued together before the barrier, the loads
+  // held it up.  So kEarly of them go out there and the others kGroup at a time
+  // between the filter's groups of frames (19 series x 488 subbands x 8192
+  // frames: 621 -> 507 ns per frame and CU; 64 x 244 x 16384: 440 -> 424; with
+  // every address the same it would be 392).
+  constexpr int kEarly = NR / 2, kGroup = NR > 5 ? 1 : 2;
   const int tid = threadIdx.x;
   const int wave = tid >> 6, lane = tid & 63;
   const int n = tid;  // FIR column
@@ -165,11 +176,13 @@ __global__ __launch_bounds__(kSynThreads) void syn_kernel(
         const_cast<float2 *>(ds), 0, (int)ser_bytes, kRawBufferWord3);
     const int n_chunk = (int)(seg / 16);
     float2 pre[NR];
-    auto fetch = [&](long mc_) {
+    // Inputs r0 .. r1 - 1 of the wave's frame of the chunk at mc_.
+    auto fetch = [&](long mc_, int r0 = 0, int r1 = NR) {
       typedef unsigned u2 __attribute__((ext_vector_type(2)));
       const unsigned mo = (unsigned)(mc_ + wave) * 8u;
 #pragma unroll
       for (int r = 0; r < NR; ++r) {
+        if (r < r0 || r >= r1) continue;
         const u2 b = __builtin_amdgcn_raw_buffer_load_b64(
             drs, roff_s[64 * r + lane] + mo, 0, 0);
         pre[r] = make_float2(__uint_as_float(b.x), __uint_as_float(b.y));
@@ -231,8 +244,9 @@ __global__ __launch_bounds__(kSynThreads) void syn_kernel(
           sl[816] = a3;
         }
       }
-      // Next chunk's inputs are in flight meanwhile.
-      if (c + 1 < n_chunk) fetch(mc + 16);
+      // The next chunk's inputs (past the segment's end: read, within the
+      // series' view, and not used).
+      fetch(mc + 16, 0, kEarly);
       __syncthreads();  // every frame of the chunk is transformed
       if (c == -1 && m0 == 0) {
         // Every history read of this block happened above: store the new
@@ -246,6 +260,7 @@ __global__ __launch_bounds__(kSynThreads) void syn_kernel(
       if (c < 0) {
 #pragma unroll
         for (int fi = 0; fi < 16; ++fi) win[fi] = lds[fi * kSynFs + pad16(no)];
+        fetch(mc + 16, kEarly, NR);
         __syncthreads();  // reads done before the next chunk's transforms
         continue;
       }
@@ -282,12 +297,16 @@ __global__ __launch_bounds__(kSynThreads) void syn_kernel(
             zr[i] = fmaf(g[t], w.x, zr[i]);
             zi[i] = fmaf(g[t], w.y, zi[i]);
           }
+        __builtin_amdgcn_sched_barrier(0);
+        fetch(mc + 16, kEarly + kGroup * (f0 / 4), kEarly + kGroup * (f0 / 4) + kGroup);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int fi = f0 + i;
           win[fi] = cur[i];
           if (!MASKED || fi >= first_valid) acc_s = fmaf(zr[i], zr[i], acc_s);
-          if (SERIES) xo[(long)fi * 1024] = zr[i];
+          // (past the cache, which the inputs need: 120 -> 111 us at 3 series)
+          if (SERIES) __builtin_nontemporal_store(zr[i], xo + (long)fi * 1024);
           reinterpret_cast<float *>(col + fi * kSynFs)[ecomp] =
               zr[i] * zr[i] + zi[i] * zi[i];
         }
