@@ -27,10 +27,10 @@
 // chunk, after the barrier), FIR sums in eight independent chains, a store of
 // the series that is no branch where it is not asked for, butterflies in FMA
 // form, and the next inputs requested before the barrier; then by 2 to 18 %,
-more with more subbands, by spreading those requests over the filter.  Tried and
-slower: inputs read by rows and handed over through LDS (three barriers, 3640
-us), two halves of eight frames of which one is transformed while the other is
-filtered (4017 us),
+// more with more subbands, by spreading those requests over the filter.  Tried and
+// slower: inputs read by rows and handed over through LDS (three barriers, 3640
+// us), two halves of eight frames of which one is transformed while the other is
+// filtered (4017 us),
 // envelope maxima in registers with the two barriers side by side (3944 to
 // 4359 us), pass 0 of the next chunk under the arg-max reads (3741), the
 // square roots of a chunk by one wave (3667).
