@@ -452,11 +452,12 @@ def trial_group_leg(a, ctx, p, cfg, blk, x, ms_all):
 
 
 def ppf_bytes_per_iteration(n_sb: int, n_frames: int) -> float:
-    """HBM bytes one LSMR iteration must move per series: H reads v and
-    reads/writes h, hbar, x (FP32, F frames of 1024) and reads/writes u
-    (complex FP32, n_sb x n_frames); H^T reads u and reads/writes v."""
+    """Bytes one LSMR iteration moves per series: H reads v and reads/writes
+    h, hbar and, every second time, x (FP32, F frames of 1024) and
+    reads/writes u (complex FP32, n_sb x n_frames); H^T reads u and
+    reads/writes v."""
     F = n_frames - 15
-    return F * 1024 * 4 * (1 + 6 + 2) + n_sb * n_frames * 8 * (2 + 1)
+    return F * 1024 * 4 * (1 + 5 + 2) + n_sb * n_frames * 8 * (2 + 1)
 
 
 def ppf_leg(a, ctx, p, cfg, stream):
