@@ -3,6 +3,7 @@
 #include <cstdarg>
 #include <cstring>
 
+#include "fft_dev.h"
 #include "lp_internal.h"
 
 namespace lp {
@@ -154,6 +155,17 @@ lp_status plan_wait(PlanBase *p, hipStream_t st) {
 void plan_release(lp_ctx *ctx, PlanBase *p) {
   std::lock_guard<std::mutex> g(ctx->mu);
   if (p->refs > 0) --p->refs;
+}
+
+// ------------------------------------------------------------- twiddles
+
+// Thread j: w^j, from the coarse and the fine part of j, and its powers 2, 4
+// and 8, each the rounded square of the one before.
+__global__ void tw_powers_kernel(float2 *tw) {
+  const int j = threadIdx.x;
+  float2 *p = tw + kTwPowers + 4 * j;
+  float2 w = cmul(tw[16 * (j >> 4)], tw[j & 15]);
+  for (int i = 0; i < 4; ++i, w = cmul(w, w)) p[i] = w;
 }
 
 // ---------------------------------------------------------------- chirp
@@ -383,9 +395,13 @@ lp_status lp_ctx_create(int32_t hip_device, lp_ctx **out) {
     double a = -2.0 * M_PI * i / 4096.0;
     tw[i] = make_float2((float)std::cos(a), (float)std::sin(a));
   }
-  LP_HIP(hipMalloc(&ctx->tw4096.p, 4096 * sizeof(float2)));
+  LP_HIP(hipMalloc(&ctx->tw4096.p, kTwEntries * sizeof(float2)));
   LP_HIP(hipMemcpy(ctx->tw4096.p, tw.data(), 4096 * sizeof(float2),
                    hipMemcpyHostToDevice));
+  hipLaunchKernelGGL(tw_powers_kernel, dim3(1), dim3(256), 0, nullptr,
+                     ctx->tw4096.as<float2>());
+  LP_HIP(hipGetLastError());
+  LP_HIP(hipStreamSynchronize(nullptr));
   lp_status rc = trig_scratch_attach(hip_device);
   if (rc) return rc;
   *out = ctx.release();

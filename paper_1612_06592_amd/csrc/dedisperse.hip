@@ -9,16 +9,21 @@
 // One 256-thread workgroup per (beam, subband, hop).  Each thread owns 16
 // points; the 4096-point transform is three radix-16 Stockham passes with
 // two exchanges through a padded 34 KB LDS tile.  The butterflies take the
-// powers 1, 2, 4 and 8 of a pass's twiddle, each rounded from the exact value:
-// pass 1's from a small LDS table, pass 2's per thread (tables of all 15 powers were measured slower: this
-// kernel is close to bound by LDS instructions as well as VALU).  The forward
-// spectrum stays in registers across all trials.  A trial's chirp phase is
-// formed per bin from FP64-reduced constants and taken through the
-// hardware sine and cosine; on a uniform grid only the first trial's is,
-// and trial t + 1's chirp is trial t's times a per-bin factor read from a
-// table formed in FP64 (a table of every trial's factors, one complex load
-// per bin and trial instead of the phase, made the single-trial workloads
-// slower: C3 2.70 -> 2.79 ms).
+// powers 1, 2, 4 and 8 of a pass's twiddle from the context's table: pass 1's
+// through LDS, pass 2's per thread (tables of all 15 powers were measured
+// slower: this kernel is close to bound by LDS instructions as well as VALU).
+// Those powers are squares of each other in FP32, and their rounding is most
+// of the outputs' error (5.7e-7 relative): rounded from the exact values they
+// would give 2.6e-7, but every output would move by 6e-7, and a series' SNR by
+// up to 9e-7, from what this transform has returned since its powers were
+// formed as products in the kernel.
+// The forward spectrum stays in registers across all trials.  A trial's chirp
+// phase is formed per bin from FP64-reduced constants and taken through the
+// hardware sine and cosine; on a uniform grid only the first trial's is, and
+// trial t + 1's chirp is trial t's times a per-bin factor read from a table
+// formed in FP64 (a table of every trial's factors, one complex load per bin
+// and trial instead of the phase, made the single-trial workloads slower: C3
+// 2.70 -> 2.79 ms).
 #include <cmath>
 
 #include "fft_dev.h"
@@ -38,7 +43,8 @@ struct DdTw {
 // 4096-point transform of v[r] = in[j + 256 r] (j = thread); on return
 // v[r] = out[j + 256 r] (HI: only r >= 8).  Unnormalised; INV selects
 // exp(+2 pi i ...).
-// pass2_twiddle(j) gives w^j and its powers.  START: pass 0's first stage (the pairs v[n], v[n + 8]) is done.
+// pass2_twiddle(j) gives w^j and its powers.  START: pass 0's first stage
+// (the pairs v[n], v[n + 8]) is done.
 template <bool INV, bool HI, bool START, typename Pass2>
 __device__ __forceinline__ void fft4096(float2 *v, float2 *lds,
                                         const DdTw &tw, Pass2 pass2_twiddle,
@@ -89,8 +95,7 @@ __device__ __forceinline__ float2 chirp(float c) {
 }
 
 // base + e folded into [-1/2, 1/2] with one rounding: e (a multiple of 1/4)
-// less a whole number is exact.  Near zero a phase keeps more bits (the
-// outputs' error against 64 bits is set by this rounding).
+// less a whole number is exact.  Near zero a phase keeps more bits.
 __device__ __forceinline__ float fold_phase(float base, float e) {
   return base + (e - rintf(base + e));
 }
@@ -126,25 +131,25 @@ __attribute__((amdgpu_waves_per_eu(4, 8))) void dd_kernel(
     int n_tec, long n_t, int n_hop, long n_blocks, int stream) {
   __shared__ float2 lds[kDdLds];
   __shared__ DdTw tws;
-  if (threadIdx.x < 16) {  // tw[n] = w^n, n < 4096
-    const int i = 16 * threadIdx.x;
-    tws.p1[threadIdx.x] = {tw[i], tw[2 * i], tw[4 * i], tw[8 * i]};
-  }
+  const Tw16 *twp = reinterpret_cast<const Tw16 *>(tw + kTwPowers);
+  if (threadIdx.x < 16) tws.p1[threadIdx.x] = twp[16 * threadIdx.x];
   // The pass-2 twiddle w^j: kept in registers, except beside the trial
   // steps' 32 (REC), where each pass reads it again (8 KB, from the caches)
   // ahead of the exchange.
-  const Tw16 w2p = {tw[threadIdx.x], tw[2 * threadIdx.x], tw[4 * threadIdx.x],
-                    tw[8 * threadIdx.x]};
+  const Tw16 w2p = twp[threadIdx.x];
   const __amdgpu_buffer_rsrc_t twrs = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<float2 *>(tw), 0, kNfft * 8, kRawBufferWord3);
+      const_cast<float2 *>(tw), 0, kTwEntries * 8, kRawBufferWord3);
   auto pass2_twiddle = [&](int jo) {
     if constexpr (!REC) return w2p;
-    auto at = [&](int n) {
-      typedef unsigned u2 __attribute__((ext_vector_type(2)));
-      const u2 b = __builtin_amdgcn_raw_buffer_load_b64(twrs, 8 * n, 0, 0);
-      return make_float2(__uint_as_float(b.x), __uint_as_float(b.y));
+    typedef unsigned u4 __attribute__((ext_vector_type(4)));
+    const u4 a = __builtin_amdgcn_raw_buffer_load_b128(twrs, 32 * jo,
+                                                       8 * kTwPowers, 0),
+             b = __builtin_amdgcn_raw_buffer_load_b128(twrs, 32 * jo,
+                                                       8 * kTwPowers + 16, 0);
+    auto f2 = [](unsigned x, unsigned y) {
+      return make_float2(__uint_as_float(x), __uint_as_float(y));
     };
-    return Tw16{at(jo), at(2 * jo), at(4 * jo), at(8 * jo)};
+    return Tw16{f2(a.x, a.y), f2(a.z, a.w), f2(b.x, b.y), f2(b.z, b.w)};
   };
   // (the barrier inside the first transform orders these before use)
   const long bid = xcd_remap(blockIdx.x, n_blocks);
@@ -280,12 +285,10 @@ __attribute__((amdgpu_waves_per_eu(4, 8))) void dd_single_kernel(
   for (int r = 0; r < 8; ++r)
     last[r] = h0 == 0 ? tl[256 * r] : ys[(long)(h0 - 1) * kHop + 256 * r];
   read(h0);
-  if (j < 16) {  // tw[n] = w^n, n < 4096
-    const int i = 16 * j;
-    tws.p1[j] = {tw[i], tw[2 * i], tw[4 * i], tw[8 * i]};
-  }
+  const Tw16 *twp = reinterpret_cast<const Tw16 *>(tw + kTwPowers);
+  if (j < 16) tws.p1[j] = twp[16 * j];
   // (the barrier inside the first transform orders these before use)
-  const Tw16 w2p = {tw[j], tw[2 * j], tw[4 * j], tw[8 * j]};
+  const Tw16 w2p = twp[j];
   auto pass2_twiddle = [&](int) { return w2p; };
   const __amdgpu_buffer_rsrc_t grs = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<float *>(gq), 0, n_sb * kNfft * 4, kRawBufferWord3);

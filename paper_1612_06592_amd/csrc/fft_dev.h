@@ -208,9 +208,7 @@ __device__ __forceinline__ void dft16_fma(float2 *v) {
   dft16_tail<INV, NZ>(v);
 }
 
-// The external twiddle of a radix-16 butterfly: w and its powers 2, 4 and 8,
-// each rounded from the exact value (squaring w three times would take twelve
-// instructions and end eight times further off).
+// The external twiddle of a radix-16 butterfly: w and its powers 2, 4 and 8.
 struct Tw16 {
   float2 w, w2, w4, w8;
   template <bool CONJ>

@@ -21,6 +21,8 @@ constexpr double kC = 299792458.0;  // speed of light, m/s
 constexpr int kM = LP_M;
 constexpr int kTaps = LP_TAPS;
 constexpr int kNfft = LP_NFFT;
+constexpr int kTwPowers = kNfft;      // the parts of the context's table of
+constexpr int kTwEntries = kNfft + 4 * 256;  // twiddles (lp_ctx::tw4096)
 constexpr int kHop = LP_HOP;
 constexpr int kDelay = LP_DELAY;
 constexpr int kHist = kNfft - kHop;   // overlap-save history per series
@@ -176,7 +178,9 @@ enum PlanKind : uint8_t { kPlanBf = 1, kPlanDd, kPlanSyn, kPlanTs };
 struct lp_ctx {
   int device = 0;
   int n_cu = 256;     // compute units of the device
-  lp::DevBuf tw4096;  // float2 exp(-2 pi i n / 4096), n < 4096
+  lp::DevBuf tw4096;  // float2 w^n, w = exp(-2 pi i / 4096), n < 4096; then,
+                      // from kTwPowers on, the powers 1, 2, 4, 8 of w^j, j <
+                      // 256, by squaring (see dedisperse.hip)
   std::mutex mu;      // guards everything below
   uint64_t tick = 0;
   size_t plan_max = 64;          // cached plans kept beyond those held
