@@ -40,7 +40,9 @@ namespace lp {
 constexpr int kPpfThreads = 1024;
 constexpr int kPpfFs = 1090;       // LDS stride of one packed frame (float2)
 constexpr int kPpfChunk = 32;      // real frames per chunk
-constexpr int kPpfNormParts = 2048; // partial sums of ||y||^2 per series
+constexpr int kPpfNormParts = 2048; // partial sums of ||y||^2 per series (FP32)
+constexpr int kPpfNormRuns = kPpfNormParts / 2;  // and of ||u||^2, ||v||^2 (FP64)
+constexpr int kPpfMaxRuns = 2048;  // runs per series where no norm is formed
 constexpr int kPpfStateBytes = 128;
 // Frames per series of the operators: with nf <= 2^19 every byte offset
 // into one series' arrays (and into its n_sb <= 511 rows of nf complex
@@ -151,18 +153,33 @@ __device__ __forceinline__ void fft1024_wave(float2 *fr, const float2 *tw_p1,
   }
 }
 
+// A thread's part of a squared norm: squares in FP32 over a group of frames
+// whose place in the series is fixed (32 in H, 16 in H^T), the groups in FP64.
+// However the series is cut into runs, the same FP32 numbers are added in
+// FP64, so the cut (and with it the number of series and of CUs) leaves the
+// norms alone to 1e-15, which the FP32 scales made of them do not show.
+struct NormAcc {
+  float group = 0.f;
+  double sum = 0.0;
+  __device__ __forceinline__ void close() {
+    sum += (double)group;
+    group = 0.f;
+  }
+};
+
 // Sum of one value per thread of a 1024-thread workgroup, fixed order;
 // thread 0 stores it.
-__device__ __forceinline__ void wg_sum_store(float acc, float *red,
-                                             float *dst) {
+__device__ __forceinline__ void wg_sum_store(double acc, double *red,
+                                             double *dst) {
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    float s = 0.f;
-    for (int w = 0; w < kPpfThreads / 64; ++w) s += red[w];
-    *dst = s;
+  if (threadIdx.x < 16) {  // one value per wave
+    double s = red[threadIdx.x];
+#pragma unroll
+    for (int off = 8; off >= 1; off >>= 1) s += __shfl_xor(s, off);
+    if (threadIdx.x == 0) *dst = s;
   }
 }
 
@@ -187,14 +204,14 @@ template <int MODE, int STREAM = 0>
 __global__ __launch_bounds__(kPpfThreads) void ppf_fwd_kernel(
     const void *__restrict__ xin_, const float2 *yin, float2 *yout,
     float *__restrict__ hv, float *__restrict__ hbar, float *__restrict__ xv,
-    const LsmrState *__restrict__ st, float *__restrict__ part,
+    const LsmrState *__restrict__ st, double *__restrict__ part,
     const short *__restrict__ kbin, const float *__restrict__ taps,
     const float2 *__restrict__ tw, int n_sb, long nf, int per_wg, int n_part,
     int iter = 0, float oscale = 1.f, int olim = 0,
     short2 *__restrict__ sout = nullptr) {
   __shared__ float2 lds[16 * kPpfFs];
   __shared__ float2 tw_p1[kTwP1], tw_p2[kTwP2];
-  __shared__ float red[16];
+  __shared__ double red[16];
 
   const int series = blockIdx.y;
   const long m0 = (long)blockIdx.x * per_wg;
@@ -252,7 +269,7 @@ __global__ __launch_bounds__(kPpfThreads) void ppf_fwd_kernel(
 #pragma unroll
   for (int i = 1; i < 16; ++i)  // frames m0 - 15 .. m0 - 1 (zero if < 0)
     ring[i] = ldx((int)(m0 - 16 + i) * kM + (kM - 1 - tid)) * sc;
-  float acc = 0.f;
+  NormAcc acc;
   const long m1 = min(m0 + per_wg, nf);
   for (long mc = m0; mc < m1; mc += kPpfChunk) {
     const int ro = opaque(tid);
@@ -381,18 +398,19 @@ __global__ __launch_bounds__(kPpfThreads) void ppf_fwd_kernel(
             const float2 qn = make_float2(val[e].x - qs * q0.x,
                                           val[e].y - qs * q0.y);
             ystore(ob + 8 * e, qn);
-            acc = fmaf(qn.x, qn.x, fmaf(qn.y, qn.y, acc));
+            acc.group = fmaf(qn.x, qn.x, fmaf(qn.y, qn.y, acc.group));
           } else {
             const float2 y0 = yload(ob + 8 * e);
             const float rx = y0.x - val[e].x, ry = y0.y - val[e].y;
-            acc = fmaf(rx, rx, fmaf(ry, ry, acc));
+            acc.group = fmaf(rx, rx, fmaf(ry, ry, acc.group));
           }
         }
       }
     }
+    acc.close();
   }
   if (MODE == kFwdLsmr || MODE == kFwdResid)
-    wg_sum_store(acc, red, part + (long)series * n_part + blockIdx.x);
+    wg_sum_store(acc.sum, red, part + (long)series * n_part + blockIdx.x);
 }
 
 // H^T (kAdjPlain: xout = H^T y) or one LSMR half-step (kAdjLsmr: p =
@@ -402,13 +420,13 @@ __global__ __launch_bounds__(kPpfThreads) void ppf_fwd_kernel(
 template <int MODE>
 __global__ __launch_bounds__(kPpfThreads) void ppf_adj_kernel(
     const float2 *__restrict__ yin, float *pio,
-    const LsmrState *__restrict__ st, float *__restrict__ part,
+    const LsmrState *__restrict__ st, double *__restrict__ part,
     const short *__restrict__ binmap, const float *__restrict__ taps,
     const float2 *__restrict__ tw, int n_sb, long nf, int per_wg,
     int n_part) {
   __shared__ float2 lds[16 * kPpfFs];
   __shared__ float2 tw_p1[kTwP1], tw_p2[kTwP2];
-  __shared__ float red[16];
+  __shared__ double red[16];
   // Element offset si nf in y of the subband feeding bin j + 64 q of the
   // packed spectrum (q < 8: bin k = j + 64 q; q >= 8: its mirror 1024 - k),
   // or -1: [q][j].
@@ -450,7 +468,7 @@ __global__ __launch_bounds__(kPpfThreads) void ppf_adj_kernel(
     ring[i] = 0.f;
     g[i] = taps[i * kM + tid];
   }
-  float acc = 0.f;
+  NormAcc acc;
   const int n_chunk = (int)((wend - j0 + kPpfChunk - 1) / kPpfChunk);
   for (int c = 0; c < n_chunk; ++c) {
     const long mc = j0 + (long)c * kPpfChunk;
@@ -531,15 +549,19 @@ __global__ __launch_bounds__(kPpfThreads) void ppf_adj_kernel(
         ring[(8 * g8 + i) & 15] = cur[i];
         if (MODE == kAdjLsmr) {
           a[i] = fmaf(-vs, pold[i], a[i]);
-          if (off[i] != 0xfffffff0u) acc = fmaf(a[i], a[i], acc);
+          // (frame mc + 8 g8 + i - 15 starts a group of 16; mc is a multiple)
+          if ((8 * g8 + i + 1) % 16 == 0) acc.close();
+          if (off[i] != 0xfffffff0u) acc.group = fmaf(a[i], a[i], acc.group);
         }
         __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(a[i]), rp, off[i],
                                               0, 0);
       }
     }
   }
-  if (MODE == kAdjLsmr)
-    wg_sum_store(acc, red, part + (long)series * n_part + run);
+  if (MODE == kAdjLsmr) {
+    acc.close();
+    wg_sum_store(acc.sum, red, part + (long)series * n_part + run);
+  }
 }
 
 // Partial sums of |y|^2 (kPpfNormParts contiguous slices per series).
@@ -565,7 +587,8 @@ __global__ __launch_bounds__(256) void ppf_sumsq_kernel(
 }
 
 // FP64 sum of n partials by one wave (fixed order; every lane gets it).
-__device__ __forceinline__ double wave_sum(const float *part, int n) {
+template <typename T>
+__device__ __forceinline__ double wave_sum(const T *part, int n) {
   double s = 0.0;
   for (int i = threadIdx.x; i < n; i += 64) s += (double)part[i];
 #pragma unroll
@@ -592,7 +615,7 @@ __global__ void lsmr_init_beta_kernel(const float *__restrict__ part,
 }
 
 // alpha_1 = ||H^T u_1||, and the initial rotation state.
-__global__ void lsmr_init_alpha_kernel(const float *__restrict__ part,
+__global__ void lsmr_init_alpha_kernel(const double *__restrict__ part,
                                        int n_part,
                                        LsmrState *__restrict__ st,
                                        double *anorm, int anorm_stride) {
@@ -615,7 +638,7 @@ __global__ void lsmr_init_alpha_kernel(const float *__restrict__ part,
 }
 
 // beta_{k+1} = ||u_{k+1}|| (unnormalised q); scales for the adjoint step.
-__global__ void lsmr_beta_kernel(const float *__restrict__ part, int n_part,
+__global__ void lsmr_beta_kernel(const double *__restrict__ part, int n_part,
                                  LsmrState *__restrict__ st) {
   const int series = blockIdx.x;
   const double b2 = wave_sum(part + (long)series * n_part, n_part);
@@ -632,7 +655,7 @@ __global__ void lsmr_beta_kernel(const float *__restrict__ part, int n_part,
 
 // alpha_{k+1} = ||p_{k+1}||, rotations P_k and Pbar_k, and the update
 // coefficients of iteration k.
-__global__ void lsmr_alpha_kernel(const float *__restrict__ part, int n_part,
+__global__ void lsmr_alpha_kernel(const double *__restrict__ part, int n_part,
                                   LsmrState *__restrict__ st, double *anorm,
                                   int anorm_stride, int k) {
   const int series = blockIdx.x;
@@ -644,7 +667,7 @@ __global__ void lsmr_alpha_kernel(const float *__restrict__ part, int n_part,
     S.p_scale = S.q_scale = 0.f;
     S.c_x_prev = S.c_x;
     S.c_hbar = S.c_x = S.c_h = 0.f;
-      st[series] = S;
+    st[series] = S;
     if (an) an[k] = an[k - 1];
     return;
   }
@@ -701,7 +724,7 @@ __global__ __launch_bounds__(256) void lsmr_final_kernel(
   x[o] = fmaf(S.c_x, hv[o] - S.c_hbar * hb0, v);
 }
 
-__global__ void ppf_rnorm_kernel(const float *__restrict__ part, int n_part,
+__global__ void ppf_rnorm_kernel(const double *__restrict__ part, int n_part,
                                  double *__restrict__ out) {
   const int series = blockIdx.x;
   const double r2 = wave_sum(part + (long)series * n_part, n_part);
@@ -811,14 +834,15 @@ __global__ __launch_bounds__(256) void station_transpose_vec_kernel(
 struct PpfRuns {
   int per_wg = 0, n_wg = 0;
 };
-static PpfRuns ppf_runs(int n_cu, int n_series, long frames, bool adj) {
-  const long most = std::min<long>(kPpfNormParts, (frames + 31) / 32);
+static PpfRuns ppf_runs(int n_cu, int n_series, long frames, bool adj,
+                        long most_runs) {
+  const long most = std::min<long>(most_runs, (frames + 31) / 32);
   PpfRuns best;
   double cost = 0.0;
   auto consider = [&](long chunks) {
     const long w = adj ? 32 * chunks - 16 : 32 * chunks;
     const long n = (frames + w - 1) / w;
-    if (n > kPpfNormParts) return;
+    if (n > most_runs) return;
     const double r = (double)n * n_series / n_cu;
     const double rounds = r <= 3.0 ? std::ceil(r) : r + 0.5;
     const double c = rounds * (chunks + (adj ? 0.0 : 0.5)) *
@@ -850,8 +874,8 @@ static PpfLayout ppf_layout(int n_sb, int n_series, long nf) {
   PpfLayout L;
   L.F = nf - (kTaps - 1);
   L.N = L.F * kM;
-  // (at most kPpfNormParts in use; a frame count past the operators' limit is
-  // sized all the same)
+  // (at most kPpfNormParts FP32 or kPpfNormRuns FP64 words in use; a frame
+  // count past the operators' limit is sized all the same)
   L.n_part = (int)std::max<long>((nf + 255) / 256, kPpfNormParts);
   size_t o = 0;
   L.st = o;
@@ -914,7 +938,7 @@ extern "C" lp_status lp_ppf_analyze(lp_ctx *ctx, const lp_band *band,
       (rc = plan_wait(p.get(), st)))
     return rc;
   const long nf = n_frames;
-  const PpfRuns rf = ppf_runs(ctx->n_cu, n_series, nf, false);
+  const PpfRuns rf = ppf_runs(ctx->n_cu, n_series, nf, false, kPpfMaxRuns);
   hipLaunchKernelGGL(ppf_fwd_kernel<kFwdAnalyze>, dim3(rf.n_wg, n_series),
                      dim3(kPpfThreads), 0, st, x, (const float2 *)nullptr,
                      static_cast<float2 *>(y), nullptr, nullptr, nullptr,
@@ -941,7 +965,7 @@ extern "C" lp_status lp_ppf_adjoint(lp_ctx *ctx, const lp_band *band,
       (rc = plan_wait(p.get(), st)))
     return rc;
   const long nf = n_frames, F = nf - (kTaps - 1);
-  const PpfRuns ra = ppf_runs(ctx->n_cu, n_series, F, true);
+  const PpfRuns ra = ppf_runs(ctx->n_cu, n_series, F, true, kPpfMaxRuns);
   hipLaunchKernelGGL(ppf_adj_kernel<kAdjPlain>, dim3(ra.n_wg, n_series),
                      dim3(kPpfThreads), 0, st,
                      static_cast<const float2 *>(y), x, nullptr, nullptr,
@@ -981,7 +1005,8 @@ extern "C" lp_status lp_ppf_invert(lp_ctx *ctx, const lp_band *band,
     return rc;
   char *w = static_cast<char *>(work);
   LsmrState *st = reinterpret_cast<LsmrState *>(w + L.st);
-  float *part = reinterpret_cast<float *>(w + L.part);
+  double *part = reinterpret_cast<double *>(w + L.part);
+  float *ypart = reinterpret_cast<float *>(w + L.part);  // before the others
   float2 *q = reinterpret_cast<float2 *>(w + L.q);
   float *pv = reinterpret_cast<float *>(w + L.p);
   float *hv = reinterpret_cast<float *>(w + L.h);
@@ -992,8 +1017,8 @@ extern "C" lp_status lp_ppf_invert(lp_ctx *ctx, const lp_band *band,
   const float *taps = p->taps.as<const float>();
   const float2 *tw = ctx->tw4096.as<const float2>();
   const int an_stride = n_iter + 1;
-  const PpfRuns rf = ppf_runs(ctx->n_cu, n_series, nf, false),
-                ra = ppf_runs(ctx->n_cu, n_series, L.F, true);
+  const PpfRuns rf = ppf_runs(ctx->n_cu, n_series, nf, false, kPpfNormRuns),
+                ra = ppf_runs(ctx->n_cu, n_series, L.F, true, kPpfNormRuns);
   const dim3 gf(rf.n_wg, n_series), ga(ra.n_wg, n_series), blk(kPpfThreads);
 
   // H stores u_k and p_k for the adjoint and the adjoint for H: kept in the
@@ -1011,9 +1036,9 @@ extern "C" lp_status lp_ppf_invert(lp_ctx *ctx, const lp_band *band,
                                              : ppf_fwd_kernel<kFwdLsmr, 3>;
   // beta_1 u_1 = y; alpha_1 v_1 = H^T u_1.
   hipLaunchKernelGGL(ppf_sumsq_kernel, dim3(kPpfNormParts, n_series),
-                     dim3(256), 0, hs, yv, (long)S * nf, part);
+                     dim3(256), 0, hs, yv, (long)S * nf, ypart);
   hipLaunchKernelGGL(lsmr_init_beta_kernel, dim3(n_series), dim3(64), 0, hs,
-                     part, st);
+                     ypart, st);
   hipLaunchKernelGGL(ppf_adj_kernel<kAdjLsmr>, ga, blk, 0, hs, yv, pv, st,
                      part, bmap, taps, tw, S, nf, ra.per_wg, ra.n_wg);
   hipLaunchKernelGGL(lsmr_init_alpha_kernel, dim3(n_series), dim3(64), 0, hs,
@@ -1083,7 +1108,7 @@ extern "C" lp_status lp_station_ppf(lp_ctx *ctx, const lp_band *band,
       (rc = plan_wait(p.get(), st)))
     return rc;
   const long nf = n_frames + 2 * (kTaps - 1);   // frames of H's output
-  const PpfRuns rf = ppf_runs(ctx->n_cu, n_in, nf, false);
+  const PpfRuns rf = ppf_runs(ctx->n_cu, n_in, nf, false, kPpfMaxRuns);
   short2 *stage = static_cast<short2 *>(work);
   hipLaunchKernelGGL(ppf_fwd_kernel<kFwdStation>, dim3(rf.n_wg, n_in),
                      dim3(kPpfThreads), 0, st, adc, (const float2 *)nullptr,
