@@ -10,8 +10,8 @@
 // LP_FP32 does the same sums in FP32 with v_mfma_f32_16x16x4_f32.
 #include <cmath>
 #include <cstring>
-#include <initializer_list>
 #include <type_traits>
+#include <utility>
 
 #include "lp_internal.h"
 
@@ -139,10 +139,12 @@ __device__ __forceinline__ float lane_swap1(float v) {
 }
 
 // LDS row stride (bytes) of the staged kernel's raw tile: KS*16 samples
-// plus 16 bytes.  For int8 rows the stride in 32-bit words is 4 KS + 4;
-// lanes (row r, quarter kq) then read words r (4 KS + 4) + 4 ks + kq.
+// plus 16 bytes, or 32 where that makes the stride an odd number of 16-byte
+// units.  Lane (row r, quarter kq) of an int8 tile reads word r stride / 4 + 4
+// ks + kq: with an odd number the 16 rows fall on distinct banks, and with an
+// even one (4 KS + 4 words, KS odd) on as few as one in 16 of them.
 __host__ __device__ inline int bf_row_stride(int KS, int isz) {
-  return KS * 16 * isz + 16;
+  return KS * 16 * isz + (KS * isz % 2 == 0 ? 16 : 32);
 }
 
 typedef int intx4 __attribute__((ext_vector_type(4)));
@@ -156,20 +158,20 @@ template <> struct VecT<4> { typedef int type; };
 // out WM x WN over (16-row m-tiles, 16-column n-tiles); each wave keeps its
 // NPW n-tiles of weight fragments in registers for all of its tiles.  The
 // tile's raw integer rows are staged in LDS as loaded (rows of KS*16
-// samples, zero padded, plus 16 bytes so row-per-lane fragment reads fall
+// samples, zero padded, at a stride that puts row-per-lane fragment reads
 // on distinct banks) and converted to FP16 as each A fragment is read; the
 // next tile is loaded into registers (NV vectors of VB bytes per thread)
 // while the current one is multiplied and stored.
-template <typename IT, int VB, int NPW, int KSM, int NV>
+template <typename IT, int VB, int NPW, int KS, int NV>
 __global__ __launch_bounds__(kBfThreads) void bf_mfma_kernel(
     const IT *__restrict__ x, const half4 *__restrict__ wf,
     const _Float16 *__restrict__ xscale, int scaled, float2 *__restrict__ y,
-    int n_sb, long n_t, long x_nt, int RK, int KS, int NT, int wn_shift,
+    int n_sb, long n_t, long x_nt, int RK, int NT, int wn_shift,
     int n_beams, int T, int tiles_per_wg, float inv_vpr) {
   typedef typename VecT<VB>::type V;
   constexpr int EPV = VB / (int)sizeof(IT);      // samples per vector
   extern __shared__ __attribute__((aligned(16))) unsigned char smb[];
-  const int RSB = bf_row_stride(KSM, (int)sizeof(IT));
+  const int RSB = bf_row_stride(KS, (int)sizeof(IT));
   _Float16 *xs_lds = reinterpret_cast<_Float16 *>(smb + T * RSB);
   const int s = blockIdx.y;
   const int tid = threadIdx.x;
@@ -181,32 +183,28 @@ __global__ __launch_bounds__(kBfThreads) void bf_mfma_kernel(
   const int nvec = T * RK / EPV;
   const int vpr = RK / EPV;  // load vectors per time row
 
-  half4 wreg[NPW][KSM];
+  half4 wreg[NPW][KS];
 #pragma unroll
   for (int p = 0; p < NPW; ++p) {
     int nt = wn + p * WN;
 #pragma unroll
-    for (int ks = 0; ks < KSM; ++ks) {
+    for (int ks = 0; ks < KS; ++ks) {
       half4 z = {0, 0, 0, 0};
-      wreg[p][ks] = (nt < NT && ks < KS)
-                        ? wf[((long)(s * NT + nt) * KS + ks) * 64 + lane]
-                        : z;
+      wreg[p][ks] =
+          nt < NT ? wf[((long)(s * NT + nt) * KS + ks) * 64 + lane] : z;
     }
   }
-  // Samples RK .. KSM*16-1 of each row multiply zero weights (the weight
-  // fragments of k-steps KS .. KSM-1 are zero too); they are zeroed once
-  // (the tiles never write them), as are the scale factors past KS*16.
-  // Every k-step then runs unconditionally.
-  // (A row and its padding are whole 32-bit words.)
-  const int padw = (KSM * 16 - RK) * (int)sizeof(IT) / 4;
+  // Samples RK .. KS*16-1 of each row multiply zero weights; they are zeroed
+  // once (the tiles never write them), so that every k-step runs
+  // unconditionally.  (A row and its padding are whole 32-bit words.)
+  const int padw = (KS * 16 - RK) * (int)sizeof(IT) / 4;
   for (int i = tid; i < T * padw; i += kBfThreads) {
     const int row = i / padw;
     *reinterpret_cast<unsigned *>(smb + row * RSB + RK * (int)sizeof(IT) +
                                   4 * (i - row * padw)) = 0u;
   }
   if (scaled)
-    for (int i = tid; i < KSM * 16; i += kBfThreads)
-      xs_lds[i] = i < KS * 16 ? xscale[i] : (_Float16)0.0f;
+    for (int i = tid; i < KS * 16; i += kBfThreads) xs_lds[i] = xscale[i];
 
   // LDS byte offset of each of this thread's load vectors within a tile
   // (the same for every tile; -1 past the tile).  row = v / vpr through
@@ -263,7 +261,7 @@ __global__ __launch_bounds__(kBfThreads) void bf_mfma_kernel(
 #pragma unroll
       for (int p = 0; p < NPW; ++p) acc[p] = floatx4{0, 0, 0, 0};
 #pragma unroll
-      for (int ks = 0; ks < KSM; ++ks) {
+      for (int ks = 0; ks < KS; ++ks) {
         // Samples ks*16 + 4*kq .. + 3 of the lane's row.
         half2v h[2];
         if constexpr (sizeof(IT) == 1) {
@@ -633,6 +631,16 @@ lp_status get_bf_plan(lp_ctx *ctx, const lp_array *a, const lp_band *band,
   return LP_OK;
 }
 
+// f(0), f(1) .. f(N - 1), each with its number as a constant.
+template <typename F, int... I>
+static void for_each_of(F &&f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>()), ...);
+}
+template <int N, typename F>
+static void for_each_int(F &&f) {
+  for_each_of(f, std::make_integer_sequence<int, N>());
+}
+
 template <typename IT>
 static lp_status launch_bf(const BfPlan *p, const void *x, long x_nt,
                            long n_t, int n_sb, void *y, hipStream_t st) {
@@ -659,20 +667,7 @@ static lp_status launch_bf(const BfPlan *p, const void *x, long x_nt,
     // more workgroups in flight), four otherwise: measured on MI355X.
     const int tpw = tiles >= 8 ? (NT == 1 ? 2 : 4) : 1;
     dim3 grid((unsigned)((tiles + tpw - 1) / tpw), n_sb);
-    // k-steps per kernel instance (KSM >= KS; the extra ones multiply
-    // zeros): the LDS rows hold KSM*16 samples.  Few inputs get their own
-    // instances: padded to 6 k-steps, they spent their time zeroing the
-    // padding (8 int16 inputs, 32 x 4096: 11.8 -> 6.8 us; 16 int8 inputs, 244
-    // x 8192: 57 -> 18 us), and 9 k-steps padded to 12 took 138 instead of
-    // 114 us at the shape above.
-    auto up = [&](std::initializer_list<int> have) {
-      for (int k : have)
-        if (KS <= k) return k;
-      return 16;
-    };
-    const int ksm = vb == 16 ? up({1, 2, 3, 4, 6, 8, 9, 10, 12, 14, 16})
-                             : up({2, 4, 8, 16});
-    size_t shm = (size_t)T * bf_row_stride(ksm, (int)sizeof(IT)) + ksm * 32;
+    size_t shm = (size_t)T * bf_row_stride(KS, (int)sizeof(IT)) + KS * 32;
     auto args = [&](auto kern) {
       LP_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                  hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -680,37 +675,33 @@ static lp_status launch_bf(const BfPlan *p, const void *x, long x_nt,
       hipLaunchKernelGGL(kern, grid, dim3(kBfThreads), shm, st,
                          static_cast<const IT *>(x), p->w.as<const half4>(),
                          p->xscale.as<const _Float16>(), (int)p->scaled,
-                         static_cast<float2 *>(y), n_sb, n_t, x_nt, RK, KS,
+                         static_cast<float2 *>(y), n_sb, n_t, x_nt, RK,
                          NT, wn_shift, p->n_beams, T, tpw,
                          1.0f / (float)(row_bytes / vb));
       return LP_OK;
     };
-    // Register arrays sized to the shape: KSM weight fragments per n-tile and
-    // the load vectors per thread that rows of KSM k-steps can need.
+    // An instance for every number of k-steps and every load width: a padded
+    // k-step costs its conversion, LDS read and products, and the zeroing of
+    // its part of the rows (122 x 8192 samples: 68 int8 inputs, 9 k-steps, 19
+    // beams 61 us, in 16 k-steps 81; 18 inputs, 3 k-steps, one beam 13.2 us, in
+    // 4 k-steps 18.3).
     lp_status rc = LP_EINVAL;
     auto run = [&](auto vb_c, auto k_c) {
-      constexpr int V = decltype(vb_c)::value, K = decltype(k_c)::value;
+      constexpr int V = decltype(vb_c)::value, K = decltype(k_c)::value + 1;
       constexpr int row = K * 16 * (int)sizeof(IT);  // longest row in bytes
       constexpr int rows = row > 128 ? 64 : 128;
-      constexpr int NV = V == 16 ? (rows * row / 16 + kBfThreads - 1) / kBfThreads
-                                 : 64 / V;
+      constexpr int NV = (rows * row / V + kBfThreads - 1) / kBfThreads;
       if constexpr (row <= 256)  // (longer rows are refused)
-        rc = npw == 1 ? args(bf_mfma_kernel<IT, V, 1, K, NV>)
-                      : args(bf_mfma_kernel<IT, V, 2, K, NV>);
+        if (K == KS)
+          rc = npw == 1 ? args(bf_mfma_kernel<IT, V, 1, K, NV>)
+                        : args(bf_mfma_kernel<IT, V, 2, K, NV>);
     };
-    auto pick = [&](auto vb_c, auto... k_c) {
-      // (one of them equals ksm)
-      ((decltype(k_c)::value == ksm ? run(vb_c, k_c) : void()), ...);
-    };
-#define LP_K(n) std::integral_constant<int, n>()
     if (vb == 16)
-      pick(LP_K(16), LP_K(1), LP_K(2), LP_K(3), LP_K(4), LP_K(6), LP_K(8),
-           LP_K(9), LP_K(10), LP_K(12), LP_K(14), LP_K(16));
+      for_each_int<16>([&](auto k) { run(std::integral_constant<int, 16>(), k); });
     else if (vb == 8)
-      pick(LP_K(8), LP_K(2), LP_K(4), LP_K(8), LP_K(16));
+      for_each_int<16>([&](auto k) { run(std::integral_constant<int, 8>(), k); });
     else
-      pick(LP_K(4), LP_K(2), LP_K(4), LP_K(8), LP_K(16));
-#undef LP_K
+      for_each_int<16>([&](auto k) { run(std::integral_constant<int, 4>(), k); });
     if (rc) return rc;
   } else {
     // k-groups of four samples per lane quarter (the kernel instance's; more
