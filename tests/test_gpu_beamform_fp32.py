@@ -1,8 +1,8 @@
 """The FP32 beamformer on the matrix cores at the edges of its tiles, against
 the FP64 oracle: inputs around the k-groups of 8 inputs and the kernel
 instances, rows of every load width (4, 8 and 16 bytes) and rows that no wide
-load divides, beams around the 8-beam n-tiles, one and many units of 128 rows,
-and workgroup ranges that cross subbands.
+load divides, beams around the 8-beam n-tiles, one and many pieces of 32 or 64
+rows, and workgroup ranges that cross subbands.
 
 Tolerance: an output is a sum of 2 K products of weights rounded to FP32
 (2^-24) with one rounding per term, so its error is below about sqrt(2 K)

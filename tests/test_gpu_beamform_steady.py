@@ -1,11 +1,16 @@
-"""The FP16 beamformer where a workgroup walks several tiles (the next one loaded
+"""Both beamformers where a workgroup walks several tiles (the next one loaded
 while the present one is multiplied), against the FP64 oracle.
 
-Every kernel instance, by k-steps of 8 inputs, load width (rows that are
+FP16: every kernel instance, by k-steps of 8 inputs, load width (rows that are
 multiples of 16, 8 and 4 bytes) and one or two n-tiles to a wave; nine tiles of
 128 rows or eighteen of 64, so that the last workgroup's walk ends early.  The
 weights are rounded to FP16 (2^-11 relative), the samples are exact and the
-sums FP32: below 2^-11 relative RMS, and no element off by 1e-2 of the RMS."""
+sums FP32: below 2^-11 relative RMS, and no element off by 1e-2 of the RMS.
+
+FP32: more pieces of rows than the chip has waves, for one and several n-tiles
+and workgroups of four and eight waves; the first, a middle and the last subband
+are compared.  2 K products with one rounding each: below 2e-6 relative RMS, and
+no element off by 2e-5 of the RMS."""
 import numpy as np
 import pytest
 
@@ -53,3 +58,13 @@ def test_fp16_instances(n_in, dtype):
     for B in ([3, 25], [16, 33], [8, 17], [9, 64])[n_in // 2 % 4]:
         compare(rng, n_in, B, 2, 1024 + 128, dtype, lp.LP_FP16_MFMA,
                 n_in % 3 == 0, 2.0 ** -11, 1e-2)
+
+
+@pytest.mark.parametrize("n_in,B,S,n_t,dtype", [
+    (8, 1, 100, 16384, "ci16"), (8, 1, 100, 16384, "ci8"),
+    (24, 17, 100, 4096, "ci16"), (40, 9, 99, 4096, "ci8"),
+    (96, 37, 100, 4096, "ci16"), (96, 61, 100, 4096, "ci16"),
+    (97, 8, 70, 4096, "ci16"), (128, 64, 40, 8192, "ci8")])
+def test_fp32_walks(n_in, B, S, n_t, dtype):
+    compare(np.random.default_rng(n_in * 100 + B), n_in, B, S, n_t, dtype,
+            lp.LP_FP32, False, 2e-6, 2e-5)
