@@ -270,8 +270,9 @@ __attribute__((amdgpu_waves_per_eu(4, 8))) void dd_single_kernel(
   float2 *tl = tail + bs * kHist + j;
   float2 *out = d + bs * n_t + j;
 
-  // Samples and outputs pass the cache by: so many hops are over 256 MB each
-  // (19 beams x 488 subbands x 4 hops: 411 -> 389 us).
+  // Samples and outputs pass the cache by: each is 256 MB or more here (19
+  // beams x 488 subbands x 4 hops: 411 -> 389 us; 32 x 128 x 4, 256 MB, 196 ->
+  // 186, with the synthesis that reads them 617 -> 609).
   float2 last[8], next[8];
   auto read = [&](int h) {
 #pragma unroll
@@ -381,8 +382,11 @@ lp_status dd_launch(lp_ctx *ctx, DdPlan *p, int n_sb, const void *y,
   // the samples read ahead pay for the start, with sixteen workgroups per CU
   // so that the last ones cost little.  Shorter runs lose: 244 series of 32
   // hops took 81 us in runs of 2 against 77 us hop by hop.
+  // Results below 256 MB, which a device of fewer than 256 CUs would reach
+  // here, stay hop by hop, and with that in the cache for their reader.
   const int per_wg = (int)std::min<long>(n_hop, nb / (16L * ctx->n_cu));
-  if (nj == 1 && per_wg >= 4) {
+  const size_t bytes = (size_t)nb * nj * kHop * sizeof(float2);
+  if (nj == 1 && per_wg >= 4 && bytes >= kMallBytes) {
     const int runs = (n_hop + per_wg - 1) / per_wg;
     const long n_wg = (long)n_beams * n_sb * runs;
     hipLaunchKernelGGL(dd_single_kernel, dim3((unsigned)n_wg),
@@ -404,7 +408,7 @@ lp_status dd_launch(lp_ctx *ctx, DdPlan *p, int n_sb, const void *y,
                      p->afac.as<const float>() + jo,
                      p->rstep.as<const float2>(),
                      p->gq.as<const float>(), n_sb, nj, n_t, n_hop, nb,
-                     (size_t)nb * nj * kHop * sizeof(float2) > kMallBytes);
+                     bytes > kMallBytes);
   LP_HIP(hipGetLastError());
   return LP_OK;
 }
