@@ -87,8 +87,9 @@ typedef int32_t lp_status;
 #define LP_CI16 2 /* complex int16: (re, im) int16 pairs                   */
 
 /* Beamformer arithmetic. */
-#define LP_FP32 0      /* FP32 inputs, weights and accumulation on the FP32
-                          matrix instructions                              */
+#define LP_FP32 0      /* FP32 inputs, weights and accumulation, on the FP32
+                          matrix instructions or (few inputs or beams) the
+                          vector ALUs                                      */
 #define LP_FP16_MFMA 1 /* FP16 inputs and weights, FP32 accumulation on the
                           matrix cores                                     */
 

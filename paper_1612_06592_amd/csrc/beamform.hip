@@ -315,7 +315,98 @@ __global__ __launch_bounds__(kBfThreads) void bf_mfma_kernel(
   }
 }
 
-// --------------------------------------------------------- FP32 kernel
+// -------------------------------------------------------- FP32 kernels
+
+constexpr int kBf32Group = 8;  // beams accumulated per pass over a row
+
+// LP_FP32 on the vector ALUs, for the calls that are bound by memory (see
+// fp32_on_valu).  Grid: x = tiles of 256 time rows, y = subband.  The tile's
+// raw integer samples are staged in LDS, by loads of neighbouring lanes on
+// neighbouring addresses, at a row stride that is an odd number of 32-bit words
+// (conflict-free row-per-lane reads); the weights [K][B] follow.  A thread
+// forms all beams of one row, eight per pass over it.
+template <typename IT, int VB>
+__global__ __launch_bounds__(kBfThreads) void bf_fp32_valu_kernel(
+    const IT *__restrict__ x, const float2 *__restrict__ w,
+    float2 *__restrict__ y, int n_sb, long n_t, long x_nt, int n_in,
+    int n_beams, int row_words) {
+  extern __shared__ int smi[];
+  const int RK = 2 * n_in;
+  const int row_bytes = RK * (int)sizeof(IT);
+  int *xs = smi;  // [256][row_words]
+  float2 *ws = reinterpret_cast<float2 *>(smi + kBfThreads * row_words);
+  const int s = blockIdx.y;
+  const long t0 = (long)blockIdx.x * kBfThreads;
+  const int rows = (int)min((long)kBfThreads, n_t - t0);
+  const char *base =
+      reinterpret_cast<const char *>(x + ((long)s * x_nt + t0) * RK);
+  const int vec_per_row = row_bytes / VB;
+  const int nvec = rows * vec_per_row;
+  for (int v = threadIdx.x; v < nvec; v += kBfThreads) {
+    int row = v / vec_per_row, c = v - row * vec_per_row;
+    int q[VB / 4];
+    __builtin_memcpy(q, base + (size_t)v * VB, VB);
+#pragma unroll
+    for (int i = 0; i < VB / 4; ++i) xs[row * row_words + c * (VB / 4) + i] = q[i];
+  }
+  const float2 *wsrc = w + (long)s * n_in * n_beams;
+  for (int i = threadIdx.x; i < n_in * n_beams; i += kBfThreads) ws[i] = wsrc[i];
+  __syncthreads();
+  const int t = threadIdx.x;
+  if (t >= rows) return;
+  const int *xr = xs + t * row_words;
+  for (int b0 = 0; b0 < n_beams; b0 += kBf32Group) {
+    float ar[kBf32Group], ai[kBf32Group];
+#pragma unroll
+    for (int k = 0; k < kBf32Group; ++k) ar[k] = ai[k] = 0.f;
+    for (int i = 0; i < n_in; ++i) {
+      float re, im;
+      if constexpr (sizeof(IT) == 1) {
+        int word = xr[i >> 1];
+        int sh = (i & 1) * 16;
+        re = (float)(signed char)(word >> sh);
+        im = (float)(signed char)(word >> (sh + 8));
+      } else {
+        int word = xr[i];
+        re = (float)(short)(word & 0xffff);
+        im = (float)(short)(word >> 16);
+      }
+      const float2 *wi = ws + i * n_beams + b0;
+#pragma unroll
+      for (int k = 0; k < kBf32Group; ++k) {
+        if (b0 + k < n_beams) {
+          float2 wv = wi[k];
+          ar[k] = fmaf(re, wv.x, ar[k]);
+          ar[k] = fmaf(-im, wv.y, ar[k]);
+          ai[k] = fmaf(re, wv.y, ai[k]);
+          ai[k] = fmaf(im, wv.x, ai[k]);
+        }
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < kBf32Group; ++k)
+      if (b0 + k < n_beams)
+        y[((long)(b0 + k) * n_sb + s) * n_t + t0 + t] =
+            make_float2(ar[k], ai[k]);
+  }
+}
+
+// Calls that the vector-ALU kernel does faster: few inputs, of which the
+// matrix kernel pads 16 samples to a k-group, and one or two beams of rows that
+// are no whole k-groups of its lanes, where its per-row loads cost more than
+// the sums.  (Not by the length of the call: a stream's chunks are to come out
+// alike.)  us, vector ALUs / matrix: 122 subbands x 8192, 2 int8 inputs, 1 and
+// 37 beams 8.5 / 11.9 and 51 / 61, 61 beams 105 / 99; 4 inputs, 24 beams 36 /
+// 39; 6 inputs, 1 and 4 beams 10.9 / 11.2, 13.9 / 11.8; 20 inputs, 1, 2 and 4
+// beams 21.3 / 24.8, 23.0 / 24.8, 25.7 / 25.2; 36 inputs, one beam 33.9 / 36.8,
+// 48 inputs 41.8 / 37.4; 311 x 4992, 20 int16 inputs, 1 and 2 beams 32 / 43 and
+// 35 / 44; 24 inputs, 1 and 2 beams 37.6 / 43.8, 42.0 / 44.3; 32 inputs, one
+// beam 55 / 51.
+static bool fp32_on_valu(int n_in, int n_beams, int row_bytes) {
+  if (n_in <= 4) return n_in * n_beams <= 100;
+  return n_in > 8 && n_in <= 28 && n_in % 16 != 0 &&
+         n_beams <= (row_bytes <= 80 ? 2 : 1);
+}
 
 // Four consecutive samples (one k-group of a lane) as FP32, exact.
 template <typename IT>
@@ -352,23 +443,22 @@ __device__ __forceinline__ void buffer_words(__amdgpu_buffer_rsrc_t rs,
 
 // LP_FP32: the same real GEMM on the FP32 matrix instructions (FP32 inputs,
 // weights and accumulation).  What bounds it is the FP32 multiply rate, 32
-// FMA per cycle and SIMD; the vector-ALU kernel it replaces read its weights
-// from LDS once per beam and input and reached 1/15 of that (96 int16 inputs,
-// 37 beams, 122 x 8192 samples: 2716 -> 267 us, 106 TFLOP/s; one beam of 48
-// int8 inputs, 122 x 16384: 77 -> 71 us, bound by memory).
+// FMA per cycle and SIMD; the vector-ALU kernel reads its weights from LDS once
+// per beam and input and reaches 1/15 of that (96 int16 inputs, 37 beams, 122 x
+// 8192 samples: 2716 -> 267 us, 106 TFLOP/s; one beam of 48 int8 inputs, 122 x
+// 16384: 77 -> 71 us, bound by memory).
 //
 // A wave owns pieces of 16 MT rows of one subband and walks the 16-column
 // n-tiles; the subband's weights sit in LDS as B fragments.  A workgroup
-// takes a contiguous range of the subband-major list of pieces (about one
-// workgroup per slot of the chip, so there is no last round) and fills the
-// weights anew where its range enters a subband.  The order of the k index
+// takes a contiguous range of the subband-major list of pieces (few ranges per
+// CU, so that the weights are seldom filled) and fills the weights anew where
+// its range enters a subband.  The order of the k index
 // is free, so lane (row, q) of an A fragment takes samples q 4 GM .. q 4 GM +
 // 4 GM - 1 of its row, one contiguous piece that it loads itself (no LDS, no
 // barrier between subbands) one step ahead and converts once for all n-tiles.
 // Samples past the row's 2 K meet zero weights; the raw buffer view ends with
 // the piece, where reads return zero.  Loads are as wide as divides both a
-// lane's part and the row, so that none lies across that end; rows of other
-// lengths are read word by word.
+// lane's part and the row, so that none lies across that end.
 template <typename IT, int GM, int MT>
 __global__ __launch_bounds__(512) void bf_fp32_kernel(
     const IT *__restrict__ x, const float2 *__restrict__ w,
@@ -381,7 +471,6 @@ __global__ __launch_bounds__(512) void bf_fp32_kernel(
   const int wave = tid >> 6, lane = tid & 63;
   const int col16 = lane & 15, q = lane >> 4;
   const unsigned row_bytes = 2u * n_in * sizeof(IT);
-  const bool wide = row_bytes % (4 * W) == 0;
   const int per_sb = (int)(n_t / (16 * MT));  // pieces of a subband
   const long total = (long)per_sb * n_sb;
   long g = (long)blockIdx.x * per_wg;
@@ -401,8 +490,10 @@ __global__ __launch_bounds__(512) void bf_fp32_kernel(
 #pragma unroll
       for (int m = 0; m < MT; ++m) {
         const unsigned off = (16 * m + col16) * row_bytes + q * (4 * NW);
-        if (wide)
+        if (W == 4 && row_bytes % 16 == 0)
           buffer_words<NW, W>(rs, off, raw[m]);
+        else if (W >= 2 && row_bytes % 8 == 0)
+          buffer_words<NW, W >= 2 ? 2 : 1>(rs, off, raw[m]);
         else
           buffer_words<NW, 1>(rs, off, raw[m]);
       }
@@ -703,15 +794,37 @@ static lp_status launch_bf(const BfPlan *p, const void *x, long x_nt,
     else
       for_each_int<16>([&](auto k) { run(std::integral_constant<int, 4>(), k); });
     if (rc) return rc;
+  } else if (fp32_on_valu(n_in, p->n_beams, row_bytes)) {
+    const int row_words = (row_bytes / 4) | 1;  // odd stride: no bank conflicts
+    const size_t shm = (size_t)kBfThreads * row_words * 4 +
+                       (size_t)n_in * p->n_beams * sizeof(float2);
+    const dim3 grid((unsigned)((n_t + kBfThreads - 1) / kBfThreads), n_sb);
+    auto kern = vb == 16  ? bf_fp32_valu_kernel<IT, 16>
+                : vb == 8 ? bf_fp32_valu_kernel<IT, 8>
+                          : bf_fp32_valu_kernel<IT, 4>;
+    hipLaunchKernelGGL(kern, grid, dim3(kBfThreads), shm, st,
+                       static_cast<const IT *>(x), p->w.as<const float2>(),
+                       static_cast<float2 *>(y), n_sb, n_t, x_nt, n_in,
+                       p->n_beams, row_words);
   } else {
     // k-groups of four samples per lane quarter (the kernel instance's; more
     // inputs than 16 GM / 2 need the next one up).
-    const int g_need = (RK + 15) / 16;
     const int NT = p->NT;
+    int g_need = (RK + 15) / 16;
+    // One n-tile of int8 rows is bound by its loads, which are single words
+    // where a lane's part is an odd number of them: it takes the next even
+    // instance (40 inputs, one beam, 122 x 8192: 40.4 -> 36.8 us; 56: 54.1 ->
+    // 46).  Below 5 groups the wider instance has fewer waves and loses.
+    if (sizeof(IT) == 1 && NT == 1 && g_need > 4) g_need += g_need & 1;
     auto args = [&](auto kern, int gm, int mt) {
-      // Workgroups per CU by the weights' LDS and the registers (two waves
-      // per SIMD from GM = 9 on, more below); where the weights take more
-      // than half of the LDS, one workgroup of 8 waves.
+      // Workgroups per CU by the weights' LDS, and by measurement rather than
+      // by residency (5 or 4 waves per SIMD up to GM 2, 4 or 3 up to GM 10, 2
+      // from GM 12 on): ranges for 8 and 4 where fewer are resident fill the
+      // chip's tail, and at GM 9 and 10 two are enough.  us, this table / the
+      // residencies, 122 x 8192, 37 beams: 8 int16 inputs 61 / 67, 24 80 / 86,
+      // 32 97 / 107, 40 122 / 115, 48 140 / 133, 80 222 / 233, 64 and 96 alike.
+      // Where the weights take more than half of the LDS, one workgroup of 8
+      // waves.
       const size_t shm = (size_t)NT * gm * 1024;
       const int threads = shm > kLdsMax / 2 ? 512 : 256, waves = threads / 64;
       const int by_regs = gm <= 2 ? 8 : gm <= 4 ? 4 : gm <= 8 ? 3 : 2;
