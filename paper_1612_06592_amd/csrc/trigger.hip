@@ -117,12 +117,15 @@ __device__ __forceinline__ int wg_exscan(int v, int *scratch, int *total) {
 // list, so the list is in time order.
 __device__ __forceinline__ void series_step(
     const SynCand *__restrict__ cand, const float *__restrict__ psum,
-    long n_t, long frame0, long warm, float k_sigma, WorkLayout w, int q,
+    int n_t, long frame0, long warm, float k_sigma, WorkLayout w, int q,
     unsigned *bits) {  // bits: n_t / 32 words of LDS
   __shared__ double sred[kT1Threads / 64];
   __shared__ float fred[kT1Threads / 64];
   __shared__ int ired[kT1Threads / 64];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  // (the wave's number in a scalar register: the 64 windows of a load start at a
+  // scalar address)
+  const int tid = threadIdx.x, lane = tid & 63,
+            wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const SynCand *cq = cand + (long)q * n_t;
   const float *pq = psum + (long)q * (n_t / 16);
 
@@ -130,23 +133,23 @@ __device__ __forceinline__ void series_step(
   // formed.
   constexpr int kU = 16;
   float ev[kU];
-  auto batch = [&](long base0) {
+  auto batch = [&](int base0) {
 #pragma unroll
     for (int u = 0; u < kU; ++u) {
-      const long m = base0 + (long)u * kT1Threads + lane;
-      ev[u] = m < n_t ? cq[m].emax : 0.0f;
+      const int base = base0 + u * kT1Threads;  // n_t is a multiple of 64
+      ev[u] = base < n_t ? (cq + base)[lane].emax : 0.0f;
     }
   };
-  batch((long)wave * 64);
+  batch(wave * 64);
 
   // sigma: fixed-order FP64 sum of the per-16-frame partial sums.
-  const long n_part = n_t / 16;
+  const int n_part = n_t / 16;
   double acc = 0.0;
-  for (long i = tid; i < n_part; i += 4 * kT1Threads) {
+  for (int i = tid; i < n_part; i += 4 * kT1Threads) {
     float v[4];  // in flight together; added in order
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const long k = i + (long)u * kT1Threads;
+      const int k = i + u * kT1Threads;
       v[u] = k < n_part ? pq[k] : 0.0f;
     }
 #pragma unroll
@@ -157,8 +160,8 @@ __device__ __forceinline__ void series_step(
   __syncthreads();
   double tot = 0.0;
   for (int i = 0; i < kT1Threads / 64; ++i) tot += sred[i];
-  const long first_valid = warm > frame0 ? warm - frame0 : 0;
-  const long n_valid_fr = first_valid >= n_t ? 0 : n_t - first_valid;
+  const int first_valid = (int)(warm > frame0 ? warm - frame0 : 0);
+  const int n_valid_fr = first_valid >= n_t ? 0 : n_t - first_valid;
   const float sigma =
       n_valid_fr > 0 ? (float)sqrt(tot / ((double)n_valid_fr * kM)) : 0.0f;
   const float thr = k_sigma * sigma;
@@ -167,15 +170,14 @@ __device__ __forceinline__ void series_step(
   // Pass A (sixteen 64-window groups per wave and step: their loads are in
   // flight together; with four, one series of 65536 windows took 24 us).
   float pk = 0.0f;  // largest maximum: over sigma below (division is monotonic)
-  for (long base0 = (long)wave * 64; base0 < n_t;
-       base0 += (long)kT1Threads * kU) {
-    if (base0 >= (long)kT1Threads * kU) batch(base0);
+  for (int base0 = wave * 64; base0 < n_t; base0 += kT1Threads * kU) {
+    if (base0 >= kT1Threads * kU) batch(base0);
 #pragma unroll
     for (int u = 0; u < kU; ++u) {
-      const long base = base0 + (long)u * kT1Threads;
-      const long m = base + lane;
+      const int base = base0 + u * kT1Threads;
+      const int m = base + lane;
       const float e = ev[u];
-      bool valid = m < n_t && m >= first_valid && sigma > 0.0f;
+      bool valid = base < n_t && m >= first_valid && sigma > 0.0f;
       if (valid) pk = fmaxf(pk, e);
       unsigned long long b = __ballot(valid && e > thr);
       if (lane == 0 && base < n_t) {
@@ -190,29 +192,29 @@ __device__ __forceinline__ void series_step(
   __syncthreads();
 
   // Pass B.
-  const long nw = (n_t + 31) / 32;
-  const long per = (nw + kT1Threads - 1) / kT1Threads;
-  const long w0 = (long)tid * per, w1 = min(nw, w0 + per);
-  auto starts_of = [&](long wi) {
+  const int nw = (n_t + 31) / 32;
+  const int per = (nw + kT1Threads - 1) / kT1Threads;
+  const int w0 = tid * per, w1 = min(nw, w0 + per);
+  auto starts_of = [&](int wi) {
     unsigned b = bits[wi];
     unsigned prev = wi > 0 ? bits[wi - 1] >> 31 : 0u;
     return b & ~((b << 1) | prev);
   };
   int n_runs = 0;
-  for (long wi = w0; wi < w1; ++wi) n_runs += __popc(starts_of(wi));
+  for (int wi = w0; wi < w1; ++wi) n_runs += __popc(starts_of(wi));
   int total = 0;
   int pos = wg_exscan(n_runs, ired, &total);
-  auto fired = [&](long m) { return (bits[m >> 5] >> (m & 31)) & 1u; };
+  auto fired = [&](int m) { return (bits[m >> 5] >> (m & 31)) & 1u; };
   SerEnt *list = w.ser_list + (long)q * w.cap_s;
-  for (long wi = w0; wi < w1; ++wi) {
+  for (int wi = w0; wi < w1; ++wi) {
     unsigned st = starts_of(wi);
     while (st) {
       int bit = __ffs(st) - 1;
       st &= st - 1;
-      long m = wi * 32 + bit;
-      long best = m;
+      const int m = wi * 32 + bit;
+      int best = m;
       float bv = cq[m].emax;
-      for (long e = m + 1; e < n_t && fired(e); ++e) {
+      for (int e = m + 1; e < n_t && fired(e); ++e) {
         float ev = cq[e].emax;
         if (ev > bv) {
           bv = ev;
@@ -220,7 +222,7 @@ __device__ __forceinline__ void series_step(
         }
       }
       SerEnt t;
-      t.pos = (int)(best * kM) + cq[best].arg;
+      t.pos = best * kM + cq[best].arg;
       t.peak = bv;
       list[pos++] = t;  // pos < n_t / 2: runs are separated by a gap
     }
@@ -592,7 +594,9 @@ struct TrigArgs {
   float *sigma_out;
 };
 
-__global__ __launch_bounds__(kT1Threads) void trig_series_kernel(TrigArgs a) {
+// (Registers for two workgroups to a CU: 600 beams of 3 trials 55 -> 41 us.)
+__global__ __launch_bounds__(kT1Threads, 8) void trig_series_kernel(
+    TrigArgs a) {
   extern __shared__ unsigned dyn[];
   series_step(a.cand, a.psum, a.n_t, a.frame0, a.warm, a.k_sigma, a.w,
               blockIdx.x, dyn);
@@ -600,9 +604,12 @@ __global__ __launch_bounds__(kT1Threads) void trig_series_kernel(TrigArgs a) {
 
 // One workgroup per beam: SERIES (one trial) forms its series first, OUTPUT
 // (one beam) writes the list as well.  A step's workspace words are read back
-// by the workgroup that wrote them, after a barrier.
+// by the workgroup that wrote them, after a barrier.  (More beams than CUs: the
+// registers leave room for two workgroups to a CU.  1024 beams of 2048 windows,
+// hundreds of triggers each 78 -> 55 us, none 33 -> 26.)
 template <bool SERIES, bool OUTPUT>
-__global__ __launch_bounds__(kT2Threads) void trig_beam_kernel(TrigArgs a) {
+__global__ __launch_bounds__(kT2Threads, OUTPUT ? 4 : 8) void trig_beam_kernel(
+    TrigArgs a) {
   static_assert(kT1Threads == kT2Threads, "one workgroup runs every step");
   extern __shared__ unsigned dyn[];
   const int b = blockIdx.x;
