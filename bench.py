@@ -885,8 +885,8 @@ def serving_bench(a):
             svc.append(dict(zip(lens, t)))
         return svc
 
-    # The same streams at FP32 (the fused path without the matrix cores),
-    # alone, for the precision comparison.
+    # The same streams at FP32 (FP32 samples, weights and sums in the
+    # beamformer), alone, for the precision comparison.
     srv = lp.Server(ctx, arena, arena_bytes, max_slots=16, chunk_t=chunk_t)
     cfgs32 = [lp.StreamCfg(*g, dtype=lp.LP_CI8, prec=lp.LP_FP32, trig_cap=256)
               for g in args]

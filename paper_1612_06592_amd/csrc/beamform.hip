@@ -421,7 +421,8 @@ __device__ __forceinline__ void group_to_f32(const unsigned *w, float *f) {
   }
 }
 
-// NW words of a raw buffer at byte offset off, in loads of W words.
+// NW words of a raw buffer at byte offset off, in loads of W words.  (On gfx950
+// the scalar offset counts in the bounds check, and each word for itself.)
 template <int NW, int W>
 __device__ __forceinline__ void buffer_words(__amdgpu_buffer_rsrc_t rs,
                                              unsigned off, unsigned *w) {

@@ -22,7 +22,8 @@
 //     recorded bins of both frames from bins k and 1024 - k.  In LSMR mode
 //     it also forms u = H v - (alpha / beta) u_old with its squared-norm
 //     partial sums, and applies the previous iteration's elementwise
-//     update of hbar, x and h while it reads v.
+//     update of hbar and h, and in every second iteration both of x's, while
+//     it reads v.
 //   ppf_adj_kernel: the recorded bins of two frames -> one packed
 //     Hermitian spectrum -> transform -> anti-causal FIR.  In LSMR mode
 //     it forms p = H^T u - (beta / alpha) p_old and its norm partials.
@@ -822,15 +823,21 @@ __global__ __launch_bounds__(256) void station_transpose_vec_kernel(
 
 // Frames per workgroup.  A workgroup is one CU's LDS tile and walks its frames
 // in chunks of 32: H's costs its frames / 32 and about half a chunk to start,
-// H^T's needs 15 frames past its own (32 i - 16 frames fill i chunks).  Runs of
-// 256 frames are right where they fill the chip for several rounds (longer
-// ones, filling it once, measured 2-3 % slower: a slow CU then holds up the
-// whole launch, which the 10 % stands for).  Where 256 would leave CUs idle or
-// a second round nearly empty, the run that fills the chip once or twice is
-// taken: one series of 32768 frames 533 -> 345 us an LSMR iteration, of 2048
-// frames 291 -> 61 us.  Lengths stay even (H: multiples of 32), so the frame
-// pairs that share a transform, and with them every output bit, do not depend
-// on them.
+// H^T's needs 15 frames past its own (32 i - 16 frames fill i chunks).  The cost
+// is the rounds of workgroups (past three, half a round for the uneven end)
+// times a run's chunks, with 10 % on runs over 256 frames, where a slow CU holds
+// up more.  Of 256 frames and the runs that fill the chip once, twice and three
+// times the cheapest is taken: one series of 32768 frames 533 -> 345 us an LSMR
+// iteration, of 2048 frames 291 -> 61 us.  Many frames end in runs that fill it
+// once, which is right for H^T alone and for H within 3 %, while the solver,
+// whose H and H^T meet each other's last vectors in the cache, would be 1 to 4 %
+// faster in runs of 256: us with the chosen runs / with 256 frames, 8 series of
+// 32768 (runs of 1024): H^T 443 / 468, H 391 / 390, an iteration 2091 / 2029; 16
+// series (2048): 907 / 922, 750 / 774, 4167 / 4039; one of 262144 (1024): 482 /
+// 527, 396 / 395, 2096 / 2071; 8 of 16384 (256 either way): 248, 205, 1040.
+// Lengths stay even (H: multiples of 32), so the frame pairs that share a
+// transform, and with them every output bit, do not depend on them; NormAcc
+// keeps the solver's norms apart from them too.
 struct PpfRuns {
   int per_wg = 0, n_wg = 0;
 };
@@ -1115,8 +1122,8 @@ extern "C" lp_status lp_station_ppf(lp_ctx *ctx, const lp_band *band,
                      (float2 *)nullptr, nullptr, nullptr, nullptr, nullptr,
                      nullptr, p->kbin.as<const short>(),
                      p->taps.as<const float>(), ctx->tw4096.as<const float2>(),
-                     band->n_sb, nf, rf.per_wg, 0, 0, scale, dtype == LP_CI8 ? 128 : 32768,
-                     stage);
+                     band->n_sb, nf, rf.per_wg, 0, 0, scale,
+                     dtype == LP_CI8 ? 128 : 32768, stage);
   const long P = (long)band->n_sb * n_frames;
   const bool ci8 = dtype == LP_CI8;
   const dim3 tgrid((unsigned)((P + 63) / 64));
