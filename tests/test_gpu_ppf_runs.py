@@ -1,6 +1,6 @@
 """H and H^T over every way that a series is cut into workgroups' runs: lengths
-around the 32-frame chunks and the runs' ends, several series, sizes that fill
-the chip once, twice and many times.
+around the 32-frame chunks and the runs' ends, several series, sizes up to one
+round of workgroups (several rounds and longer runs: test_gpu_ppf_batch.py).
 
 The cut must not show: the same frames inside a longer series and inside many
 series (other runs) give the same bits.  And against the FP64 oracle's
